@@ -48,7 +48,6 @@ typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
 typedef __attribute__((address_space(3))) bf16x4_t lds_bf16x4_t;
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 typedef __attribute__((address_space(3))) float lds_f32;
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) f32x4_t lds_f32x4_t;
 
 // LDS tiles of both gradient kernels (K and V in dQ; Q, dO and V in dK/dV)

@@ -32,8 +32,9 @@
 // tensor, filled by direct global->LDS loads two (V) and four (K) tiles ahead,
 // with one barrier per tile.
 //
-// fp32 kernel: a plain VALU kernel (4 lanes per query row, exact running max)
-// for fp32 inputs; it exists for correctness at small sizes.
+// fp32 kernel: fp32 MFMAs (v_mfma_f32_32x32x2_f32) with an exact running max,
+// operands loaded from global memory by the lanes that feed them; the keys of a
+// query tile may be shared out over a workgroup's waves.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -96,20 +97,18 @@ struct TileRanges {
 // Rows [q0, q1) of tile `idx` among the `nt` tiles that cover the rows
 // [begin, end) of one chunk: the chunk's 32-row blocks are split as evenly as
 // possible, so every tile gets the same number of blocks give or take one
-// (at most BM / 32 since nt >= (end - begin) / BM) and tiles take about equally
-// long; only the chunk's last block may be partial.
-template <int BM>
+// and tiles take about equally long; only the chunk's last block may be
+// partial. With nt = ceil((end - begin) / BM) a tile has at most BM / 32 blocks.
 __device__ __forceinline__ void split_rows(int begin, int end, int nt, int idx, int& q0, int& q1) {
     const int blocks = (end - begin + 31) / 32;
     q0 = begin + 32 * ((idx * blocks) / nt);
     q1 = min(begin + 32 * (((idx + 1) * blocks) / nt), end);
 }
 
-template <int BM>
-__device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile) {
+__device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile, int BM) {
     TileRanges t;
     if (a.mode == 0) {
-        split_rows<BM>(0, a.Lq, a.n_qtiles, tile, t.q0, t.q1);
+        split_rows(0, a.Lq, a.n_qtiles, tile, t.q0, t.q1);
         t.n = a.n_ranges;
         t.b0 = t.e0 = t.b1 = t.e1 = 0;
         return t;
@@ -120,13 +119,13 @@ __device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile) {
     int chunk;
     if (nat < a.ref_tiles) {
         chunk = 0;
-        split_rows<BM>(0, a.ref_tok, a.ref_tiles, nat, t.q0, t.q1);
+        split_rows(0, a.ref_tok, a.ref_tiles, nat, t.q0, t.q1);
     } else {
         const int u = nat - a.ref_tiles;
         chunk = 1 + u / a.chunk_tiles;
         const int cs = a.ref_tok + (chunk - 1) * a.chunk_tok;
         const int ce = min(cs + a.chunk_tok, a.seq_len);
-        split_rows<BM>(cs, ce, (ce - cs + BM - 1) / BM, u % a.chunk_tiles, t.q0, t.q1);
+        split_rows(cs, ce, (ce - cs + BM - 1) / BM, u % a.chunk_tiles, t.q0, t.q1);
     }
     if (chunk == 0) {
         t.n = 1;
@@ -224,7 +223,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     const int bh = id / a.n_qtiles;
     const int head = bh % a.H;
     const int bat = bh / a.H;
-    const TileRanges tr = plan_tile<BM>(a, tile);
+    const TileRanges tr = plan_tile(a, tile, BM);
 
     const __bf16* qp = static_cast<const __bf16*>(a.q) + bat * a.q_sb + head * a.q_sh;
     const __bf16* kp = static_cast<const __bf16*>(a.k) + bat * a.k_sb + head * a.k_sh;
@@ -625,101 +624,241 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
 }
 
 // ----------------------------------------------------------------------------
-// fp32 VALU kernel (small problems, exact fp32 arithmetic)
+// fp32 MFMA kernel
 // ----------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const AttnArgs a) {
-    constexpr int BM = kTileRowsF32;  // 64 query rows, 4 lanes each
-    constexpr int BN = 32;
-    constexpr int DP = D / 4;         // elements per lane
-    constexpr int PSTR = DP + 1;      // padded quarter-row pitch in LDS
-    constexpr int RSTR = 4 * PSTR;
-    constexpr int C4 = D / 4;         // float4 per key row
+// The same products with v_mfma_f32_32x32x2_f32 (fp32 operands and sums), one
+// wave per 32 query rows and share of the keys. An fp32 MFMA takes 64 cycles
+// for one register per operand, so operands need no LDS: the lanes load them
+// from the cache hierarchy in the MFMA's layout (a lane's 16-byte load of a K
+// row feeds four MFMAs), K of the next key block while the current one is
+// computed. A workgroup's NW waves are split into a.key_groups groups of keys
+// and NW / key_groups groups of 32 query rows; waves of one query group merge
+// their (max, row sum, O) through LDS at the end, in a fixed order. Key groups
+// fill the chip where query rows are few and also shorten the serial chain of
+// a small call (a 32-key block takes about 1.7 us of one wave at D = 64); the
+// host picks their number. Bound by the MFMAs plus what the operand loads cost
+// (without any loads the loop is 1.3 times as fast): 2304 rows in 5 chunks, 8
+// heads, D = 64: 66 us (76 TFLOP/s; 421 us as a VALU kernel with 4 lanes per
+// row); 4000 rows, 48 heads, D = 128: 2.5 ms (86 TFLOP/s; 10.5 ms). V operands
+// loaded one register at a time, not as 16-byte vectors, cost 20% more.
+template <int D, int NW, bool VT>
+__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(const AttnArgs a) {
+    constexpr int KC = D / 8;   // K chunks: 4 dimensions per half-wave
+    constexpr int DB = D / 32;  // 32-row blocks of O^T
+    constexpr int NR = 16 * DB; // O registers per lane
+    __shared__ float part[NW / 2][NR + 2][64];
 
-    __shared__ float Ks[BN * RSTR];
-    __shared__ float Vs[BN * RSTR];
-
-    const int tid = threadIdx.x;
-    const int row = tid >> 2, part = tid & 3;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int hw = lane >> 5, l32 = lane & 31;
+    const int kgs = a.key_groups;
+    const int kg = wave % kgs, qg = wave / kgs;
     const int total = a.n_qtiles * a.B * a.H;
     const int id = xcd_logical_id(blockIdx.x, total);
     const int tile = id % a.n_qtiles;
     const int bh = id / a.n_qtiles;
     const int head = bh % a.H;
     const int bat = bh / a.H;
-    const TileRanges tr = plan_tile<BM>(a, tile);
+    const TileRanges tr = plan_tile(a, tile, 32 * (NW / kgs));
 
     const float* qp = static_cast<const float*>(a.q) + bat * a.q_sb + head * a.q_sh;
     const float* kp = static_cast<const float*>(a.k) + bat * a.k_sb + head * a.k_sh;
     const float* vp = static_cast<const float*>(a.v) + bat * a.v_sb + head * a.v_sh;
-    const int qrow = tr.q0 + row;
+    const int qrow = tr.q0 + 32 * qg + l32;
     const bool row_ok = qrow < tr.q1;
 
-    float qv[DP], ov[DP];
+    // Q^T operand: lane holds dimensions 8*kk + 4*hw .. + 3 of its query row.
+    f32x4_t qf[KC];
 #pragma unroll
-    for (int e = 0; e < DP; ++e) {
-        qv[e] = row_ok ? qp[qrow * a.q_st + part * DP + e] : 0.f;
-        ov[e] = 0.f;
-    }
-    float m = kNegInf, l = 0.f;
-    const float c = a.scale_log2;
+    for (int kk = 0; kk < KC; ++kk)
+        qf[kk] = row_ok ? *reinterpret_cast<const f32x4_t*>(qp + qrow * a.q_st + 8 * kk + 4 * hw) : f32x4_t{};
 
-    for (int r = 0; r < tr.n; ++r) {
-        const int kb = range_begin(a, tr, r), ke = range_end(a, tr, r);
-        for (int k0 = kb; k0 < ke; k0 += BN) {
-            __syncthreads();
-            for (int ch = tid; ch < BN * C4; ch += 256) {
-                const int kr = ch / C4, c4 = ch % C4;
-                float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
-                if (k0 + kr < ke) {
-                    kv = *reinterpret_cast<const float4*>(kp + (k0 + kr) * a.k_st + c4 * 4);
-                    if (!a.v_blocked)
-                        vv = *reinterpret_cast<const float4*>(vp + (k0 + kr) * a.v_st + c4 * 4);
-                }
-                const int d0 = c4 * 4;
-                const int base = kr * RSTR + (d0 / DP) * PSTR + d0 % DP;
-                Ks[base + 0] = kv.x; Ks[base + 1] = kv.y; Ks[base + 2] = kv.z; Ks[base + 3] = kv.w;
-                if (!a.v_blocked) {
-                    Vs[base + 0] = vv.x; Vs[base + 1] = vv.y; Vs[base + 2] = vv.z; Vs[base + 3] = vv.w;
-                }
-            }
-            if (a.v_blocked) {
-                // Dimension-major cache blocks: element (key, d) sits at
-                // (key / 64) * 64 * D + d * 64 + key % 64.
-                for (int e = tid; e < BN * D; e += 256) {
-                    const int d = e / BN, kr = e % BN, key = k0 + kr;
-                    Vs[kr * RSTR + (d / DP) * PSTR + d % DP] =
-                        key < ke ? vp[(key >> 6) * (64 * D) + d * 64 + (key & 63)] : 0.f;
-                }
-            }
-            __syncthreads();
-            const int n = min(BN, ke - k0);
-            for (int j = 0; j < n; ++j) {
-                const float* kr = &Ks[j * RSTR + part * PSTR];
-                float dot = 0.f;
+    // This wave's share [jb, je) of the 32-key blocks of the tile's ranges.
+    auto blocks_of = [&](int r) { return (range_end(a, tr, r) - range_begin(a, tr, r) + 31) / 32; };
+    int n = 0;
+    for (int r = 0; r < tr.n; ++r) n += blocks_of(r);
+    const int jb = n * kg / kgs, je = n * (kg + 1) / kgs;
+    const bool busy = jb < je && tr.q0 + 32 * qg < tr.q1;
+    int r = 0, k0 = 0, ke = 0;  // current range, first key of the block, end of the range
+    if (busy) {
+        int j = jb;
+        while (j >= blocks_of(r)) j -= blocks_of(r++);
+        k0 = range_begin(a, tr, r) + 32 * j;
+        ke = range_end(a, tr, r);
+    }
+
+    // K rows of the block at k0 (rows past the range end repeat its last row;
+    // their scores are masked): lane's key k0 + l32, the Q operand's
+    // dimensions. KR chunks are held, each reloaded once it is used.
+    constexpr int KR = 8;
+    f32x4_t kf[KR];
+    auto load_k = [&](int kk, const float* row) __attribute__((always_inline)) {
+        kf[kk % KR] = *reinterpret_cast<const f32x4_t*>(row + 8 * kk + 4 * hw);
+    };
+    auto k_base = [&](int first, int end) { return kp + static_cast<int64_t>(min(first + l32, end - 1)) * a.k_st; };
+    // V^T operands of key group g of the block: v[d][e] feeds the MFMA of
+    // score register 4*g + e (key 8*g + 4*hw + e of the block) into O block d,
+    // zero past the range end. Row l32 of O block d is dimension 32*d + l32
+    // with VT (a lane's 16-byte load holds 4 keys of one dimension), else
+    // DB*l32 + d (a lane's load holds DB dimensions of one key).
+    auto load_v = [&](float (&v)[DB][4], int g) __attribute__((always_inline)) {
+        if constexpr (VT) {
+            // from the first cache block of the tile (at most one block on)
+            const int at = min(k0 + 8 * g + 4 * hw, (ke - 1) & ~3) - (k0 & ~63);
+            const float* base = vp + static_cast<int64_t>(k0 >> 6) * (64 * D);
+            const uint32_t off = (at >> 6) * (64 * D) + l32 * 64 + (at & 63);
 #pragma unroll
-                for (int e = 0; e < DP; ++e) dot = fmaf(qv[e], kr[e], dot);
-                dot += __shfl_xor(dot, 1);
-                dot += __shfl_xor(dot, 2);
-                const float s = dot * c;
-                const float m_new = fmaxf(m, s);
-                const float alpha = exp2f(m - m_new);
-                const float p = exp2f(s - m_new);
-                l = fmaf(l, alpha, p);
-                const float* vr = &Vs[j * RSTR + part * PSTR];
+            for (int d = 0; d < DB; ++d) {
+                const f32x4_t w = *reinterpret_cast<const f32x4_t*>(base + off + d * 32 * 64);
 #pragma unroll
-                for (int e = 0; e < DP; ++e) ov[e] = fmaf(ov[e], alpha, p * vr[e]);
-                m = m_new;
+                for (int e = 0; e < 4; ++e) v[d][e] = w[e];
+            }
+        } else {
+            typedef float vec_t __attribute__((ext_vector_type(DB)));
+            // a wave-uniform row plus the lane's offset (0 or 4 rows on, which
+            // fits 32 bits at the largest batch * heads)
+            const bool full = k0 + 32 <= ke;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = k0 + 8 * g + e;
+                const float* base = vp + static_cast<int64_t>(full ? row : min(row, ke - 1)) * a.v_st;
+                const uint32_t rows = full ? 4 * hw : min(4 * hw, max(ke - 1 - row, 0));
+                const vec_t w = *reinterpret_cast<const vec_t*>(base + (rows * static_cast<uint32_t>(a.v_st) + DB * l32));
+#pragma unroll
+                for (int d = 0; d < DB; ++d) v[d][e] = w[d];
             }
         }
+        if (k0 + 32 > ke) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (k0 + 8 * g + 4 * hw + e >= ke) {
+#pragma unroll
+                    for (int d = 0; d < DB; ++d) v[d][e] = 0.f;
+                }
+        }
+    };
+
+    f32x16_t acc[DB];
+#pragma unroll
+    for (int d = 0; d < DB; ++d) acc[d] = f32x16_t{};
+    float m = kNegInf, l = 0.f;  // running max of the row (log2 domain), this lane's part of its sum
+    const float c = a.scale_log2;
+    if (busy) {
+        const float* row = k_base(k0, ke);
+#pragma unroll
+        for (int kk = 0; kk < KR; ++kk) load_k(kk, row);
+        for (int j = jb; j < je; ++j) {
+            int nr = r, nk0 = k0 + 32, nke = ke;
+            if (nk0 >= ke && j + 1 < je) {
+                ++nr;
+                nk0 = range_begin(a, tr, nr);
+                nke = range_end(a, tr, nr);
+            }
+            const float* next = k_base(j + 1 < je ? nk0 : k0, nke);
+            // V of the first VB key groups, in flight during the score MFMAs
+            constexpr int VB = D == 64 ? 4 : 2;
+            float v[VB][DB][4];
+#pragma unroll
+            for (int g = 0; g < VB; ++g) load_v(v[g], g);
+            // S^T = K Q^T as two chains (half the additions in sequence)
+            f32x16_t s0 = f32x16_t{}, s1 = f32x16_t{};
+#pragma unroll
+            for (int kk = 0; kk < KC; ++kk) {
+                s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[kk % KR][0], qf[kk][0], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[kk % KR][1], qf[kk][1], s1, 0, 0, 0);
+                s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[kk % KR][2], qf[kk][2], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[kk % KR][3], qf[kk][3], s1, 0, 0, 0);
+                if (kk + KR < KC) load_k(kk + KR, row);
+                else load_k(kk + KR - KC, next);
+            }
+            row = next;
+            float mx = kNegInf;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                s0[i] = (s0[i] + s1[i]) * c;
+                if (k0 + 8 * (i / 4) + 4 * hw + i % 4 >= ke) s0[i] = kNegInf;
+                mx = fmaxf(mx, s0[i]);
+            }
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            const float m_new = fmaxf(m, fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])));
+            if (__any(m_new > m)) {
+                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+                l *= alpha;
+#pragma unroll
+                for (int d = 0; d < DB; ++d) acc[d] *= alpha;
+                m = m_new;
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                s0[i] = __builtin_amdgcn_exp2f(s0[i] - m);
+                l += s0[i];
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int d = 0; d < DB; ++d)
+                        acc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[g % VB][d][e], s0[4 * g + e], acc[d], 0, 0, 0);
+                if (g + VB < 4) load_v(v[g % VB], g + VB);
+                __builtin_amdgcn_sched_barrier(0);  // no V loads further ahead (registers)
+            }
+            r = nr;
+            k0 = nk0;
+            ke = nke;
+        }
+    }
+    l += __shfl_xor(l, 32);
+
+    // Merge the key groups of a query group pairwise: the upper half of the
+    // groups hand theirs over, the lower half fold them in.
+    for (int half = kgs / 2; half >= 1; half /= 2) {
+        float(*mine)[64] = part[qg * half + kg % half];
+        if (kg >= half && kg < 2 * half) {
+#pragma unroll
+            for (int i = 0; i < NR; ++i) mine[i][lane] = acc[i / 16][i % 16];
+            mine[NR][lane] = m;
+            mine[NR + 1][lane] = l;
+        }
+        __syncthreads();
+        if (kg < half) {
+            const float m2 = mine[NR][lane];
+            const float mm = fmaxf(m, m2);
+            // a group without keys (or whose scores are all -inf) adds nothing
+            const float f1 = m == kNegInf ? 0.f : exp2f(m - mm), f2 = m2 == kNegInf ? 0.f : exp2f(m2 - mm);
+            l = l * f1 + mine[NR + 1][lane] * f2;
+#pragma unroll
+            for (int i = 0; i < NR; ++i) acc[i / 16][i % 16] = acc[i / 16][i % 16] * f1 + mine[i][lane] * f2;
+            m = mm;
+        }
+        __syncthreads();
     }
 
-    if (row_ok) {
+    if (kg == 0 && row_ok) {
         float* op = static_cast<float*>(a.o) + bat * a.o_sb + head * a.o_sh + qrow * a.o_st;
         const float inv = 1.f / l;
+        if constexpr (VT) {
 #pragma unroll
-        for (int e = 0; e < DP; ++e) op[part * DP + e] = ov[e] * inv;
-        if (a.lse != nullptr && part == 0) {
+            for (int d = 0; d < DB; ++d) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4_t w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = acc[d][4 * g + e] * inv;
+                    *reinterpret_cast<f32x4_t*>(op + 32 * d + 8 * g + 4 * hw) = w;
+                }
+            }
+        } else {
+            typedef float vec_t __attribute__((ext_vector_type(DB)));
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                vec_t w;
+#pragma unroll
+                for (int d = 0; d < DB; ++d) w[d] = acc[d][i] * inv;
+                *reinterpret_cast<vec_t*>(op + DB * (8 * (i / 4) + 4 * hw + i % 4)) = w;
+            }
+        }
+        if (a.lse != nullptr && hw == 0) {
             a.lse[(static_cast<int64_t>(bat) * a.H + head) * a.Lq + qrow] =
                 (m + log2f(l)) * 0.69314718055994530942f;
         }
@@ -748,15 +887,18 @@ hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int D, int NW>
+void launch_f32(const AttnArgs& a, hipStream_t s) {
+    const dim3 grid(a.n_qtiles * a.B * a.H), block(NW * 64);
+    if (a.v_blocked) hipLaunchKernelGGL((attn_fwd_f32_kernel<D, NW, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((attn_fwd_f32_kernel<D, NW, false>), grid, block, 0, s, a);
+}
+
 hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, hipStream_t s) {
-    const dim3 grid(a.n_qtiles * a.B * a.H), block(256);
-    if (head_dim == 128) {
-        hipLaunchKernelGGL(attn_fwd_f32_kernel<128>, grid, block, 0, s, a);
-    } else if (head_dim == 64) {
-        hipLaunchKernelGGL(attn_fwd_f32_kernel<64>, grid, block, 0, s, a);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    if (head_dim == 128 && a.key_groups <= 4) launch_f32<128, 4>(a, s);
+    else if (head_dim == 64 && a.key_groups <= 4) launch_f32<64, 4>(a, s);
+    else if (head_dim == 64 && a.key_groups == 8) launch_f32<64, 8>(a, s);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -470,8 +470,7 @@ tm_status attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
     a.Lq = int32_t(p.Lq);
     a.scale_log2 = float(double(g.scale) * 1.4426950408889634);
     a.mode = p.mode;
-    const int64_t BM = g.dtype == TM_BF16 ? tmk::kTileRowsBf16 : tmk::kTileRowsF32;
-    int64_t tiles;
+    int64_t most_keys = 0;  // keys of the query row that sees the most
     if (p.mode == 0) {
         if (p.ranges.size() > size_t(tmk::kMaxRanges))
             return fail(TM_E_SHAPE, "too many key ranges (%zu)", p.ranges.size());
@@ -480,21 +479,46 @@ tm_status attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
             a.range_begin[i] = int32_t(p.ranges[i].first);
             a.range_end[i] = int32_t(p.ranges[i].second);
         }
-        tiles = ceil_div(p.Lq, BM);
+        most_keys = range_len(p.ranges);
     } else {
-        const int64_t L = p.seq_len, nc = n_chunks(g, L);
-        a.ref_tok = int32_t(std::min(g.RT, L));
+        a.ref_tok = int32_t(std::min(g.RT, p.seq_len));
         a.chunk_tok = int32_t(g.CT);
         a.window = int32_t(g.W);
-        a.seq_len = int32_t(L);
-        a.ref_tiles = int32_t(ceil_div(a.ref_tok, BM));
-        a.chunk_tiles = int32_t(ceil_div(g.CT, BM));
-        tiles = a.ref_tiles;
+        a.seq_len = int32_t(p.seq_len);
+        most_keys = std::min(p.seq_len, g.RT + (g.W + 1) * g.CT);
+    }
+    // Query tiles of at most BM rows per (batch, head); tiles never straddle a chunk.
+    auto count_tiles = [&](int64_t BM) {
+        if (p.mode == 0) return ceil_div(p.Lq, BM);
+        const int64_t L = p.seq_len, nc = n_chunks(g, L);
+        int64_t tiles = ceil_div(a.ref_tok, BM);
         if (nc >= 2) {
-            tiles += (nc - 2) * a.chunk_tiles;
+            tiles += (nc - 2) * ceil_div(g.CT, BM);
             tiles += ceil_div(chunk_end(g, nc - 1, L) - chunk_start(g, nc - 1), BM);
         }
+        return tiles;
+    };
+    int64_t BM = tmk::kTileRowsBf16;
+    if (g.dtype == TM_F32) {
+        // Key groups: up to 4 until there are four waves per SIMD (2 fit at a
+        // time; shorter waves leave a shorter tail: 24 heads of 2304 rows at
+        // head_dim 64 take 179 us with 4 groups, 202 with 2), 8 only where
+        // that still is at most two waves per SIMD (16 heads of 903 rows: 110
+        // us with 8, 99 with 4; one head of 2304 rows: 36 with 8, 39 with 4),
+        // and no more than there are 32-key blocks.
+        const int64_t waves = count_tiles(32) * g.B * g.H;
+        int groups = 1;
+        while (groups < 4 && waves * groups < 2 * tmk::kF32FillWaves && int64_t(groups) * 64 <= most_keys)
+            groups *= 2;
+        if (g.D == 64 && groups == 4 && waves * 8 <= tmk::kF32FillWaves && 8 * 32 <= most_keys) groups = 8;
+        a.key_groups = groups;
+        BM = tmk::f32_tile_rows(groups);
     }
+    if (p.mode == 1) {
+        a.ref_tiles = int32_t(ceil_div(a.ref_tok, BM));
+        a.chunk_tiles = int32_t(ceil_div(g.CT, BM));
+    }
+    const int64_t tiles = count_tiles(BM);
     if (tiles * g.B * g.H > INT32_MAX) return fail(TM_E_SHAPE, "grid too large");
     a.n_qtiles = int32_t(tiles);
 

@@ -13,7 +13,14 @@ constexpr int kMaxRanges = 16;  // key ranges of one query segment (>= TM_MAX_WI
 // Rows per query tile of each attention kernel; the host needs them to count
 // tiles per chunk.
 constexpr int kTileRowsBf16 = 256;
-constexpr int kTileRowsF32 = 64;
+
+// The fp32 kernel's workgroups have 4 waves (8 with 8 key groups, head_dim 64
+// only), 32 query rows each; the waves are shared out between key groups and
+// query rows, so a query tile has 32 * waves / key_groups rows.
+constexpr int f32_tile_rows(int key_groups) { return 32 * (key_groups == 8 ? 8 : 4) / key_groups; }
+// Waves (32 query rows and a share of the keys each) that fill the chip: two
+// on every SIMD of its 256 CUs.
+constexpr int64_t kF32FillWaves = 2 * 4 * 256;
 
 // KV-cache pools are organised in blocks of this many token rows. The V pool
 // stores each block dimension-major: [D][kCacheBlock] per (batch, head, block),
@@ -42,6 +49,7 @@ struct AttnArgs {
     int32_t B, H, Lq;
     float scale_log2;  // softmax scale * log2(e)
     int32_t n_qtiles;  // query tiles per (batch, head)
+    int32_t key_groups;  // fp32 kernel: shares of a tile's keys (1, 2, 4 or 8)
     // mode 0: every query row of the buffer belongs to one chunk and sees the
     //         same key ranges (streaming form, or one chunk of a sequence);
     // mode 1: the buffer holds a whole sequence (row i = position i); each

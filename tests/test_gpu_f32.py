@@ -1,0 +1,80 @@
+"""GPU parity of the fp32 attention kernel where its key split changes.
+
+The kernel shares a query tile's keys out over 1, 2, 4 or 8 groups of waves,
+chosen on the host from the number of 32-row query blocks and of keys. Each
+case lands on one of them, streamed (dimension-major V from the cache) and as a
+whole sequence (row-major V), with ragged rows, ranges that end inside a
+32-key block and, in the stream, cache regions that start off 32-key blocks.
+Bar: max |gpu - oracle| <= 1e-4 x RMS, log-sum-exp within 1e-4.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import LSE_ATOL, assert_close, from_dev, say, to_dev
+from oracle import ChunkGeometry, StreamHistory, full_sequence_attention
+from synth import draw_chunk, draw_qkv_sequence
+from synth.inputs import Workload
+
+pytestmark = pytest.mark.gpu
+
+# B, H, D, T, C, R, W, frames: key groups of the whole sequence
+CASES = [
+    (1, 2, 64, 5, 1, 1, 1, 3, 1),      # 15 keys: one group whatever the fill
+    (1, 2, 128, 33, 1, 1, 1, 2, 2),    # 66 keys: two groups
+    (1, 3, 128, 41, 2, 1, 1, 6, 4),    # few rows, D = 128: four groups
+    (1, 2, 64, 41, 2, 3, 2, 9, 8),     # few rows, D = 64: eight groups
+    (8, 64, 64, 35, 1, 1, 1, 3, 2),    # 512 (batch, head) pairs of 6 blocks
+    (16, 64, 64, 33, 1, 1, 1, 3, 1),   # 1024 pairs of 6 blocks: one group
+    (8, 64, 128, 35, 1, 1, 1, 3, 2),
+    (16, 64, 128, 33, 1, 1, 1, 3, 1),
+]
+
+
+@pytest.fixture(scope="module")
+def tm():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2506_03099_amd import tm as binding
+    binding.lib()
+    return binding
+
+
+def _heads(B, H):
+    """(batch, head) pairs to compare: all of a small case, the corners of a large one."""
+    if B * H <= 16:
+        return [(b, h) for b in range(B) for h in range(H)]
+    return [(0, 0), (0, H - 1), (B // 2, 3), (B - 1, H - 1)]
+
+
+@pytest.mark.parametrize("B,H,D,T,C,R,W,frames,groups", CASES)
+def test_f32_key_groups(tm, B, H, D, T, C, R, W, frames, groups):
+    say(f"f32: B={B} H={H} D={D} T={T} C={C} R={R} W={W} frames={frames} ({groups} key groups)")
+    g = ChunkGeometry(T, C, R, W)
+    desc = tm.make_desc(B, H, D, T, C, R, W, "f32")
+    w = Workload(700 + groups, "f32_groups", "f32", B, H, D, T, C, R, W, n_frames=frames)
+    d = draw_qkv_sequence(w)
+    q, k, v = (to_dev(d[n]) for n in "qkv")
+    lse = torch.empty(B, H, frames * T, dtype=torch.float32, device="cuda")
+    o = tm.tm_sparse_causal_attn_fwd(desc, q, -1, k=k, v=v, n_frames=frames, lse=lse)
+    torch.cuda.synchronize()
+    o, lse = from_dev(o), lse.cpu().numpy()
+    for b, h in _heads(B, H):
+        one = [d[n][b:b + 1, :, h:h + 1] for n in "qkv"]
+        want, want_lse = full_sequence_attention(*one, g)
+        assert_close(o[b:b + 1, :, h:h + 1], want, "f32", f"sequence b={b} h={h}")
+        assert np.max(np.abs(lse[b, h] - want_lse[0, 0])) <= LSE_ATOL["f32"]
+
+    # streamed: chunk 2 of 2 (its last rows missing) over c_0 and the window
+    cache = tm.KVCache(desc)
+    hist = {p: StreamHistory(g) for p in _heads(B, H)}
+    for t in range(3):
+        n = None if t < 2 else max(1, C * T - 3)
+        c = draw_chunk(w, t, n)
+        qd, kd, vd = (to_dev(c[x]) for x in "qkv")
+        tm.tm_kv_append(cache, t, kd, vd)
+        for (b, h), s in hist.items():
+            s.append(t, c["k"][b:b + 1, :, h:h + 1], c["v"][b:b + 1, :, h:h + 1])
+        o = from_dev(tm.tm_sparse_causal_attn_fwd(desc, qd, t, cache=cache))
+    for (b, h), s in hist.items():
+        want = s.attend(c["q"][b:b + 1, :, h:h + 1], 2)[0]
+        assert_close(o[b:b + 1, :, h:h + 1], want, "f32", f"stream b={b} h={h}")
