@@ -48,6 +48,7 @@ namespace {
 
 typedef __attribute__((address_space(3))) bf16x4_t lds_bf16x4_t;
 typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
+typedef __attribute__((address_space(3))) f32x4_t lds_f32x4_t;
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 
 // Threads per workgroup of the bf16 kernel: 8 waves (two per SIMD) sharing
@@ -85,24 +86,25 @@ __device__ __forceinline__ float pin(float x) {
     return x;
 }
 
-// Query rows [q0, q1) of tile `tile` and its key ranges. Mode 0 reads the
+// Query rows [q0, q1) of tile `tile` and its key ranges. Mode 0 takes the
 // ranges from the kernel arguments; mode 1 derives them from the geometry.
 struct TileRanges {
     int q0, q1;
     int n;         // number of ranges
-    int b0, e0;    // mode 1 ranges (at most two)
+    int b0, e0;    // the first two ranges (a whole sequence has no more)
     int b1, e1;
 };
 
 // Rows [q0, q1) of tile `idx` among the `nt` tiles that cover the rows
 // [begin, end) of one chunk: the chunk's 32-row blocks are split as evenly as
-// possible, so every tile gets the same number of blocks give or take one
-// and tiles take about equally long; only the chunk's last block may be
+// possible, the first tiles one block larger where they do not divide evenly,
+// so tiles take about equally long; only the chunk's last block may be
 // partial. With nt = ceil((end - begin) / BM) a tile has at most BM / 32 blocks.
 __device__ __forceinline__ void split_rows(int begin, int end, int nt, int idx, int& q0, int& q1) {
     const int blocks = (end - begin + 31) / 32;
-    q0 = begin + 32 * ((idx * blocks) / nt);
-    q1 = min(begin + 32 * (((idx + 1) * blocks) / nt), end);
+    const int each = blocks / nt, more = blocks - each * nt;
+    q0 = begin + 32 * (idx * each + min(idx, more));
+    q1 = min(begin + 32 * ((idx + 1) * each + min(idx + 1, more)), end);
 }
 
 __device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile, int BM) {
@@ -110,7 +112,10 @@ __device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile, int
     if (a.mode == 0) {
         split_rows(0, a.Lq, a.n_qtiles, tile, t.q0, t.q1);
         t.n = a.n_ranges;
-        t.b0 = t.e0 = t.b1 = t.e1 = 0;
+        t.b0 = a.range_begin[0];
+        t.e0 = a.range_end[0];
+        t.b1 = a.range_begin[1];
+        t.e1 = a.range_end[1];
         return t;
     }
     // Mode 1: tiles are ordered heaviest first (the last chunks see the most
@@ -122,28 +127,22 @@ __device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile, int
         split_rows(0, a.ref_tok, a.ref_tiles, nat, t.q0, t.q1);
     } else {
         const int u = nat - a.ref_tiles;
-        chunk = 1 + u / a.chunk_tiles;
+        const int before = u / a.chunk_tiles;
+        chunk = 1 + before;
         const int cs = a.ref_tok + (chunk - 1) * a.chunk_tok;
         const int ce = min(cs + a.chunk_tok, a.seq_len);
-        split_rows(cs, ce, (ce - cs + BM - 1) / BM, u % a.chunk_tiles, t.q0, t.q1);
+        split_rows(cs, ce, (ce - cs + BM - 1) / BM, u - before * a.chunk_tiles, t.q0, t.q1);
     }
-    if (chunk == 0) {
-        t.n = 1;
-        t.b0 = 0;
-        t.e0 = a.ref_tok;
-        t.b1 = t.e1 = 0;
-    } else {
+    t.n = 1;
+    t.b0 = t.b1 = t.e1 = 0;
+    t.e0 = a.ref_tok;
+    if (chunk > 0) {
         const int lo = max(1, chunk - a.window);
         const int end = min(a.ref_tok + chunk * a.chunk_tok, a.seq_len);
         if (lo == 1) {  // c_0 and c_1 are adjacent: one range
-            t.n = 1;
-            t.b0 = 0;
             t.e0 = end;
-            t.b1 = t.e1 = 0;
         } else {
             t.n = 2;
-            t.b0 = 0;
-            t.e0 = a.ref_tok;
             t.b1 = a.ref_tok + (lo - 1) * a.chunk_tok;
             t.e1 = end;
         }
@@ -151,11 +150,15 @@ __device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile, int
     return t;
 }
 
+// Range r of a tile. A cache call (CACHE) may have up to kMaxRanges, in the
+// kernel arguments; a whole sequence has at most two, held in registers.
+template <bool CACHE>
 __device__ __forceinline__ int range_begin(const AttnArgs& a, const TileRanges& t, int r) {
-    return a.mode == 0 ? a.range_begin[r] : (r == 0 ? t.b0 : t.b1);
+    return CACHE ? a.range_begin[r] : (r == 0 ? t.b0 : t.b1);
 }
+template <bool CACHE>
 __device__ __forceinline__ int range_end(const AttnArgs& a, const TileRanges& t, int r) {
-    return a.mode == 0 ? a.range_end[r] : (r == 0 ? t.e0 : t.e1);
+    return CACHE ? a.range_end[r] : (r == 0 ? t.e0 : t.e1);
 }
 
 __device__ __forceinline__ f32x16_t mfma32x32x16(bf16x8_t a, bf16x8_t b, f32x16_t c) {
@@ -186,7 +189,7 @@ __device__ __forceinline__ int vt_swizzle(int d) { return (d >> 1) & 7; }
 template <int D, bool VT, bool OF32>
 __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const AttnArgs a) {
     constexpr int BM = kTileRowsBf16;  // query rows per workgroup
-    constexpr int BN = 64;             // keys per tile
+    constexpr int BN = kKeyTile;       // keys per tile
     constexpr int CPR = D / 8;         // 16-byte chunks per key row
     constexpr int ROWB = D * 2;        // bytes per key row
     constexpr int TILEB = BN * ROWB;
@@ -229,33 +232,33 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     const __bf16* kp = static_cast<const __bf16*>(a.k) + bat * a.k_sb + head * a.k_sh;
     const __bf16* vp = static_cast<const __bf16*>(a.v) + bat * a.v_sb + head * a.v_sh;
 
-    // ---- key tiles: the tiles of range 0, then those of range 1, ... Tile j
-    // of the walk (clamped to the last tile) is found by counting tiles per
-    // range; this runs only at range boundaries.
+    // ---- key tiles: the tiles of range 0, then those of range 1, ... A Walk
+    // stands in range r: tile j of the walk starts at key kb + BN * j as long
+    // as that lies below the range's end ke. Walks only move forward.
     struct KeyTile {
         int k0, ke;
     };
-    auto range_tiles = [&](int r) { return (range_end(a, tr, r) - range_begin(a, tr, r) + BN - 1) / BN; };
-    int n = 0;
-    for (int r = 0; r < tr.n; ++r) n += range_tiles(r);
-    auto tile_at = [&](int j) __attribute__((always_inline)) {
-        j = min(j, n - 1);
-        int r = 0, first = 0;
-        while (r + 1 < tr.n && j >= first + range_tiles(r)) {
-            first += range_tiles(r);
-            ++r;
-        }
-        return KeyTile{range_begin(a, tr, r) + (j - first) * BN, range_end(a, tr, r)};
+    struct Walk {
+        int kb, ke, r;
     };
-    // Smallest tile index >= j whose tile ends its range (the walk's last
-    // tile if there is none).
-    auto next_range_end = [&](int j) __attribute__((always_inline)) {
-        int last = 0;
-        for (int r = 0; r < tr.n; ++r) {
-            last += range_tiles(r);
-            if (last - 1 >= j) return last - 1;
+    auto range_tiles = [&](int r) {
+        return (range_end<VT>(a, tr, r) - range_begin<VT>(a, tr, r) + BN - 1) / BN;
+    };
+    int n;
+    if constexpr (VT) n = a.n_ktiles;
+    else n = range_tiles(0) + (tr.n > 1 ? range_tiles(1) : 0);
+    // one past the walk's last tile in the current range
+    auto tiles_end = [](const Walk& w) { return (w.ke - w.kb + BN - 1) / BN; };
+    // Tile j (clamped to the walk's last tile).
+    auto tile_at = [&](Walk& w, int j) __attribute__((always_inline)) {
+        int e = tiles_end(w);
+        while (j >= e && w.r + 1 < tr.n) {
+            ++w.r;
+            w.kb = range_begin<VT>(a, tr, w.r) - BN * e;
+            w.ke = range_end<VT>(a, tr, w.r);
+            e = tiles_end(w);
         }
-        return n - 1;
+        return KeyTile{w.kb + BN * min(j, e - 1), w.ke};
     };
 
     // ---- direct global->LDS loads of one tile. Rows past the range end
@@ -305,22 +308,6 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
         const uint32_t blk = lds_base + lds_wave + i * NW * 1024;
         lds_dma16x2(p0, o0, l0 + blk, p1, o1, l1 + blk);
     };
-
-    // ---- Q^T operand (B of the score MFMA): lane holds q[row][16*kk + 8*hw .. +8].
-    const int qrow = tr.q0 + wave * 32 + l32;
-    const bool row_ok = qrow < tr.q1;
-    bf16x8_t qf[KK];
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-        if (row_ok) {
-            qf[kk] = *reinterpret_cast<const bf16x8_t*>(qp + qrow * a.q_st + kk * 16 + hw * 8);
-        } else {
-            qf[kk] = bf16x8_t{};
-        }
-    }
-    // The Q loads land before any direct load is issued, so no wait that the
-    // compiler places for them can be miscounted.
-    wait_lds_dma();
 
     // ---- per-lane LDS byte offsets of the operand fragments within a tile.
     // K fragment (kk, kb): row l32 + 32*kb (permuted with VT), chunk 2*kk + hw.
@@ -420,23 +407,42 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     // ---- prologue: tiles 0..3 of K and 0..1 of V in flight, S(0) and its
     // exact maximum (the lazy running max starts from it), x(0) = S(0)*c - m.
     uint32_t offk[NI], offv[NI];  // lane offsets of the loads of the current K and V tiles
+    Walk ws{range_begin<VT>(a, tr, 0), range_end<VT>(a, tr, 0), 0};  // tile t+1 (scores)
+    const KeyTile first = tile_at(ws, 0);
+    Walk wv = ws, wk = ws;  // tiles t+2 (V loads) and t+4 (K loads)
     {
-        const KeyTile k0t = tile_at(0), k1t = tile_at(1), k2t = tile_at(2), k3t = tile_at(3);
+        Walk w = ws;
         uint32_t o0[NI], o1[NI];
-        plan(o0, false, k0t);
-        plan(o1, true, k0t);
+        plan(o0, false, first);
+        plan(o1, true, first);
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-            dma_pair(i, kbase(k0t), o0[i], kbuf(0), vbase(k0t), o1[i], NBUF * TILEB + vbuf(0));
+            dma_pair(i, kbase(first), o0[i], kbuf(0), vbase(first), o1[i], NBUF * TILEB + vbuf(0));
+        const KeyTile k1t = tile_at(w, 1);
         plan(o0, false, k1t);
         plan(o1, true, k1t);
 #pragma unroll
         for (int i = 0; i < NI; ++i)
             dma_pair(i, kbase(k1t), o0[i], kbuf(1), vbase(k1t), o1[i], NBUF * TILEB + vbuf(1));
+        const KeyTile k2t = tile_at(w, 2), k3t = tile_at(w, 3);
         plan(o0, false, k2t);
         plan(o1, false, k3t);
 #pragma unroll
         for (int i = 0; i < NI; ++i) dma_pair(i, kbase(k2t), o0[i], kbuf(2), kbase(k3t), o1[i], kbuf(3));
+    }
+    // ---- Q^T operand (B of the score MFMA): lane holds q[row][16*kk + 8*hw .. +8].
+    // Issued behind the direct loads, so that both latencies pass together; the
+    // waits the compiler places for them can only wait for more than needed.
+    const int qrow = tr.q0 + wave * 32 + l32;
+    const bool row_ok = qrow < tr.q1;
+    bf16x8_t qf[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+        if (row_ok) {
+            qf[kk] = *reinterpret_cast<const bf16x8_t*>(qp + qrow * a.q_st + kk * 16 + hw * 8);
+        } else {
+            qf[kk] = bf16x8_t{};
+        }
     }
     wait_lds_dma();
     __syncthreads();
@@ -453,7 +459,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
         xa[0] = xa[1] = f32x16_t{};
 #pragma unroll
         for (int s = 0; s < NK; ++s) xa[s & 1] = mfma32x32x16(kf[s], qf[s >> 1], xa[s & 1]);
-        mask_tile(xa, tile_at(0));
+        mask_tile(xa, first);
         m_run = row_max(xa) * c;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -481,35 +487,35 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     //
     // Tiles t+1 (scores), t+2 (V load) and t+4 (K load) move one tile on in
     // their range unless a tile among t+1..t+4 ends a range; only then (at
-    // most a few iterations per range, and at the end of the walk) are they
-    // looked up afresh, the load offsets planned again and the mask of tile
+    // most a few iterations per range, and at the end of the walk) do their
+    // walks move on, are the load offsets planned again and the mask of tile
     // t+1 decided.
     int event = 0;                 // smallest range-ending tile index >= the last refresh's t + 2
     const void* kptr = nullptr;    // K source of tile t+4
     const void* vptr = nullptr;    // V source of tile t+2
-    KeyTile ks{0, BN};             // tile t+1 when it ends its range (scores to mask)
     bool mask_next = false;
     const int64_t kstep = static_cast<int64_t>(BN) * a.k_st * 2;  // bytes per tile of keys
     const int64_t vstep = static_cast<int64_t>(BN) * (VT ? D : a.v_st) * 2;
     auto refresh = [&](int t) __attribute__((always_inline)) {
+        kptr = static_cast<const char*>(kptr) + kstep;
+        vptr = static_cast<const char*>(vptr) + vstep;
+        mask_next = false;
+        // No else branch: with one, the compiler kept two copies of the state
+        // and moved it on every iteration (12 of a tile's 260 instructions;
+        // 480p chunk 888 -> 871 us).
         if (__builtin_expect(t + 4 >= event, 0)) {
-            const KeyTile k4 = tile_at(t + 4), v2 = tile_at(t + 2);
-            ks = tile_at(t + 1);
-            mask_next = ks.k0 + BN > ks.ke;
+            const KeyTile k4 = tile_at(wk, t + 4), v2 = tile_at(wv, t + 2), s1 = tile_at(ws, t + 1);
+            mask_next = s1.k0 + BN > s1.ke;
             plan(offk, false, k4);
             plan(offv, true, v2);
             kptr = kbase(k4);
             vptr = vbase(v2);
-            event = __builtin_amdgcn_readfirstlane(next_range_end(t + 2));
+            event = __builtin_amdgcn_readfirstlane(tiles_end(wv) - 1);
             // The range bounds may come from scalar loads, which share a
             // counter with the LDS reads and complete out of order: wait for
             // them here, on this rare path, so that no full wait lands on the
             // common path where fragment reads are still in flight.
             wait_lds_reads<0>();
-        } else {
-            kptr = static_cast<const char*>(kptr) + kstep;
-            vptr = static_cast<const char*>(vptr) + vstep;
-            mask_next = false;
         }
     };
     // The barrier orders only this workgroup's LDS use: the compiler may not
@@ -552,7 +558,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
             for (int e = 0; e < 32; e += 2) form_p2(x, pf, e, (e & 2) ? lt1 : lt0);
         }
         l_run += lt0 + lt1;
-        if (mask_next) mask_tile(nx, ks);
+        if (mask_next) mask_tile(nx, tile_at(ws, t + 1));
         const float nm = -m_run;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -589,33 +595,56 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
             end_tile();
         }
     }
-    wait_lds_dma();  // no load may still be writing LDS when the workgroup ends
+    // no load may still be writing LDS; every wave is done with the tiles
+    wait_lds_dma();
+    __syncthreads();
 
     // ---- epilogue: normalise, store rows inside the tile, rounded to bf16
-    // (nearest even) or, with OF32, as the fp32 values that rounding would take
+    // (nearest even) or, with OF32, as the fp32 values that rounding would take.
+    // The rows go through the wave's share of the LDS (16-byte chunk c of row r
+    // at c ^ (r & CM)), so that they are stored whole: in the MFMA layout a
+    // store instruction would touch 32 rows for 16 or 32 bytes each (with the
+    // queries behind the direct loads above, 3 us less per workgroup: one
+    // 256-row tile over 20 key tiles 38.5 -> 35.7 us).
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     const float inv = 1.f / l_tot;
-    if (row_ok) {
-        const int64_t orow = bat * a.o_sb + head * a.o_sh + qrow * a.o_st;
+    {
+        constexpr int ES = OF32 ? 4 : 2;       // bytes per element
+        constexpr int OCPR = D * ES / 16;      // chunks per row
+        constexpr int CM = OCPR < 16 ? 7 : 15;
+        static_assert(NW * 32 * D * ES <= 2 * NBUF * TILEB, "output rows must fit the LDS");
+        lds_u8* const rows = L + __builtin_amdgcn_readfirstlane(wave) * (32 * D * ES);
+        if (busy) {
 #pragma unroll
-        for (int d = 0; d < DB; ++d) {
+            for (int d = 0; d < DB; ++d) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                if constexpr (OF32) {
-                    float4 w;
-                    w.x = acc[d][4 * g + 0] * inv;
-                    w.y = acc[d][4 * g + 1] * inv;
-                    w.z = acc[d][4 * g + 2] * inv;
-                    w.w = acc[d][4 * g + 3] * inv;
-                    *reinterpret_cast<float4*>(static_cast<float*>(a.o) + orow + 32 * d + 8 * g + 4 * hw) = w;
-                } else {
-                    bf16x4_t w;
+                for (int g = 0; g < 4; ++g) {
+                    if constexpr (OF32) {
+                        f32x4_t w;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(acc[d][4 * g + e] * inv);
-                    *reinterpret_cast<bf16x4_t*>(static_cast<__bf16*>(a.o) + orow + 32 * d + 8 * g + 4 * hw) = w;
+                        for (int e = 0; e < 4; ++e) w[e] = acc[d][4 * g + e] * inv;
+                        *(lds_f32x4_t*)(rows + l32 * (D * ES) + (((8 * d + 2 * g + hw) ^ (l32 & CM)) << 4)) = w;
+                    } else {
+                        bf16x4_t w;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(acc[d][4 * g + e] * inv);
+                        *(lds_bf16x4_t*)(rows + l32 * (D * ES) + (((4 * d + g) ^ (l32 & CM)) << 4) + 8 * hw) = w;
+                    }
                 }
             }
+            asm volatile("" ::: "memory");
+            unsigned char* const op = static_cast<unsigned char*>(a.o) + (bat * a.o_sb + head * a.o_sh) * ES;
+#pragma unroll
+            for (int i = 0; i < 32 * OCPR / 64; ++i) {
+                const int ch = 64 * i + lane, row = ch / OCPR;
+                const f32x4_t w = *(const lds_f32x4_t*)(rows + row * (D * ES) + (((ch % OCPR) ^ (row & CM)) << 4));
+                const int orow = tr.q0 + wave * 32 + row;
+                if (orow < tr.q1)
+                    *reinterpret_cast<f32x4_t*>(op + static_cast<int64_t>(orow) * a.o_st * ES + (ch % OCPR) * 16) = w;
+            }
         }
+    }
+    if (row_ok) {
         if (a.lse != nullptr && hw == 0) {
             a.lse[(static_cast<int64_t>(bat) * a.H + head) * a.Lq + qrow] =
                 (m_run + __log2f(l_tot)) * 0.69314718055994530942f;
@@ -674,7 +703,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
         qf[kk] = row_ok ? *reinterpret_cast<const f32x4_t*>(qp + qrow * a.q_st + 8 * kk + 4 * hw) : f32x4_t{};
 
     // This wave's share [jb, je) of the 32-key blocks of the tile's ranges.
-    auto blocks_of = [&](int r) { return (range_end(a, tr, r) - range_begin(a, tr, r) + 31) / 32; };
+    auto blocks_of = [&](int r) { return (range_end<VT>(a, tr, r) - range_begin<VT>(a, tr, r) + 31) / 32; };
     int n = 0;
     for (int r = 0; r < tr.n; ++r) n += blocks_of(r);
     const int jb = n * kg / kgs, je = n * (kg + 1) / kgs;
@@ -683,8 +712,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
     if (busy) {
         int j = jb;
         while (j >= blocks_of(r)) j -= blocks_of(r++);
-        k0 = range_begin(a, tr, r) + 32 * j;
-        ke = range_end(a, tr, r);
+        k0 = range_begin<VT>(a, tr, r) + 32 * j;
+        ke = range_end<VT>(a, tr, r);
     }
 
     // K rows of the block at k0 (rows past the range end repeat its last row;
@@ -751,8 +780,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
             int nr = r, nk0 = k0 + 32, nke = ke;
             if (nk0 >= ke && j + 1 < je) {
                 ++nr;
-                nk0 = range_begin(a, tr, nr);
-                nke = range_end(a, tr, nr);
+                nk0 = range_begin<VT>(a, tr, nr);
+                nke = range_end<VT>(a, tr, nr);
             }
             const float* next = k_base(j + 1 < je ? nk0 : k0, nke);
             // V of the first VB key groups, in flight during the score MFMAs

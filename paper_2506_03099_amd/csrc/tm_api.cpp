@@ -478,6 +478,7 @@ tm_status attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
         for (size_t i = 0; i < p.ranges.size(); ++i) {
             a.range_begin[i] = int32_t(p.ranges[i].first);
             a.range_end[i] = int32_t(p.ranges[i].second);
+            a.n_ktiles += int32_t(ceil_div(p.ranges[i].second - p.ranges[i].first, tmk::kKeyTile));
         }
         most_keys = range_len(p.ranges);
     } else {

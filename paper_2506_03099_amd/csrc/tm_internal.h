@@ -13,6 +13,7 @@ constexpr int kMaxRanges = 16;  // key ranges of one query segment (>= TM_MAX_WI
 // Rows per query tile of each attention kernel; the host needs them to count
 // tiles per chunk.
 constexpr int kTileRowsBf16 = 256;
+constexpr int kKeyTile = 64;  // keys per tile of the bf16 kernel
 
 // The fp32 kernel's workgroups have 4 waves (8 with 8 key groups, head_dim 64
 // only), 32 query rows each; the waves are shared out between key groups and
@@ -56,6 +57,7 @@ struct AttnArgs {
     //         tile's chunk and key ranges follow from the geometry below.
     int32_t mode;
     int32_t n_ranges;  // mode 0
+    int32_t n_ktiles;  // mode 0: 64-key tiles of all ranges
     int32_t range_begin[kMaxRanges];
     int32_t range_end[kMaxRanges];
     int32_t ref_tok;      // mode 1: R*T (clipped to the sequence)
