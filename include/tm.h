@@ -191,6 +191,23 @@ tm_status tm_sparse_causal_attn_fwd_f32out(const tm_attn_desc* desc, const void*
                                            const void* k, const void* v, int32_t n_frames,
                                            float* o, float* lse, hipStream_t stream);
 
+/* The same two calls (o_f32 = 0 or 1: o as in the first or the second) with a
+ * caller-owned workspace for the call's duration on `stream`. Query tiles that
+ * do not fill the GPU then share their keys out over several workgroups, whose
+ * partial results (fp32 O, running max and row sum) go through the workspace
+ * and are merged in a fixed order. Which calls do so, and how, follows from the
+ * arguments' sizes alone; the sum over the keys is then ordered differently
+ * from the calls without a workspace, the result still deterministic.
+ * workspace: device memory, 16-byte aligned, not overlapping any other tensor,
+ * or NULL. With fewer than tm_sparse_causal_attn_fwd_workspace() bytes (0: the
+ * call needs none; also on invalid arguments) it is not used. */
+size_t tm_sparse_causal_attn_fwd_workspace(const tm_attn_desc* desc, int32_t q_chunk,
+                                           const tm_kv_cache* cache, int32_t n_frames);
+tm_status tm_sparse_causal_attn_fwd_ws(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
+                                       const tm_kv_cache* cache, const void* k, const void* v,
+                                       int32_t n_frames, void* o, int32_t o_f32, float* lse,
+                                       void* workspace, size_t workspace_bytes, hipStream_t stream);
+
 /* Backward pass of the full-sequence form (training the student through the
  * attention of Sec. 4.2): given dO = dL/dO, the gradients
  *   dV = P^T dO, dS = P * (dO V^T - rowsum(dO * O)), dQ = scale dS K,

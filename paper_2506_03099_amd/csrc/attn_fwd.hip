@@ -220,8 +220,18 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     const int hw = lane >> 5;   // half-wave: which 8-element k-slice a lane feeds
     const int l32 = lane & 31;  // the query column (and operand row) a lane owns
 
+    // Whole tiles first, then the parts of the split ones (n_whole is a
+    // multiple of the XCDs), a tile's parts next to each other.
     const int total = a.n_qtiles * a.B * a.H;
-    const int id = xcd_logical_id(blockIdx.x, total);
+    const bool split = static_cast<int>(blockIdx.x) >= a.n_whole;
+    int id, part = 0;
+    if (!split) {
+        id = xcd_logical_id(blockIdx.x, a.n_whole);
+    } else {
+        const int sid = xcd_logical_id(blockIdx.x - a.n_whole, (total - a.n_whole) * a.parts);
+        id = a.n_whole + sid / a.parts;
+        part = sid % a.parts;
+    }
     const int tile = id % a.n_qtiles;
     const int bh = id / a.n_qtiles;
     const int head = bh % a.H;
@@ -408,6 +418,15 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     // exact maximum (the lazy running max starts from it), x(0) = S(0)*c - m.
     uint32_t offk[NI], offv[NI];  // lane offsets of the loads of the current K and V tiles
     Walk ws{range_begin<VT>(a, tr, 0), range_end<VT>(a, tr, 0), 0};  // tile t+1 (scores)
+    if (split) {
+        // A part takes tiles [j0, j1) of the walk, numbered from 0 here. (It
+        // may have none where tiles see fewer key tiles than there are parts:
+        // its row sums then stay zero.) Loads past j1 fetch tiles that exist.
+        const int j0 = n * part / a.parts, j1 = n * (part + 1) / a.parts;
+        tile_at(ws, j0);
+        ws.kb += BN * j0;
+        n = j1 - j0;
+    }
     const KeyTile first = tile_at(ws, 0);
     Walk wv = ws, wk = ws;  // tiles t+2 (V loads) and t+4 (K loads)
     {
@@ -460,7 +479,10 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
 #pragma unroll
         for (int s = 0; s < NK; ++s) xa[s & 1] = mfma32x32x16(kf[s], qf[s >> 1], xa[s & 1]);
         mask_tile(xa, first);
-        m_run = row_max(xa) * c;
+        // (a row whose scores are all -inf here starts from 0, so that it adds
+        // nothing to the rows' sums instead of making them NaN)
+        const float mx = row_max(xa);
+        m_run = mx == kNegInf ? 0.f : mx * c;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -607,6 +629,23 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     // queries behind the direct loads above, 3 us less per workgroup: one
     // 256-row tile over 20 key tiles 38.5 -> 35.7 us).
     const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (split) {
+        // unnormalised, in registers' order: every store is a whole KB
+        if (busy) {
+            const int64_t at = (static_cast<int64_t>(id - a.n_whole) * a.parts + part) * NW + wave;
+            float* const w = a.part + at * part_floats(D) + 4 * lane;
+#pragma unroll
+            for (int d = 0; d < DB; ++d)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<f32x4_t*>(w + (4 * d + g) * 256) =
+                        f32x4_t{acc[d][4 * g], acc[d][4 * g + 1], acc[d][4 * g + 2], acc[d][4 * g + 3]};
+            float* const ml = a.part + at * part_floats(D) + 32 * D;
+            ml[lane] = m_run;
+            ml[64 + lane] = l_tot;
+        }
+        return;
+    }
     const float inv = 1.f / l_tot;
     {
         constexpr int ES = OF32 ? 4 : 2;       // bytes per element
@@ -650,6 +689,83 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
                 (m_run + __log2f(l_tot)) * 0.69314718055994530942f;
         }
     }
+}
+
+// Merges the parts of the split query tiles: one wave per 32 query rows and 32
+// output dimensions. Parts are added in order (deterministic); a part whose row
+// sum is zero (no keys, or only scores of -inf) adds nothing.
+template <int D, bool OF32>
+__global__ __launch_bounds__(64) void attn_merge_kernel(const AttnArgs a) {
+    constexpr int BM = kTileRowsBf16, NW = BM / 32, DB = D / 32;
+    const int lane = threadIdx.x, hw = lane >> 5, l32 = lane & 31;
+    const int d = blockIdx.x % DB;
+    const int wave = blockIdx.x / DB % NW;
+    const int st = blockIdx.x / (DB * NW);  // split tile
+    const int id = a.n_whole + st;
+    const int tile = id % a.n_qtiles;
+    const int bh = id / a.n_qtiles;
+    const int head = bh % a.H;
+    const int bat = bh / a.H;
+    const TileRanges tr = plan_tile(a, tile, BM);
+    if (tr.q0 + wave * 32 >= tr.q1) return;
+
+    const float* p0 = a.part + (static_cast<int64_t>(st) * a.parts * NW + wave) * part_floats(D);
+    constexpr int64_t step = NW * part_floats(D);  // from part to part
+    // four parts' loads in flight together (the kernel is bound by their latency)
+    constexpr int U = 4;
+    f32x4_t acc[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[g] = f32x4_t{};
+    float m = kNegInf, l = 0.f;
+    for (int i = 0; i < a.parts; i += U) {
+        float mi[U], li[U];
+        f32x4_t ai[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float* p = p0 + min(i + u, a.parts - 1) * step;
+            mi[u] = p[32 * D + lane];
+            li[u] = p[32 * D + 64 + lane];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) ai[u][g] = *reinterpret_cast<const f32x4_t*>(p + (4 * d + g) * 256 + 4 * lane);
+        }
+        float mx = m;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i + u >= a.parts) li[u] = 0.f;
+            if (li[u] != 0.f) mx = fmaxf(mx, mi[u]);
+        }
+        const float f0 = l != 0.f ? __builtin_amdgcn_exp2f(m - mx) : 0.f;
+        l *= f0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) acc[g] *= f0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float f = li[u] != 0.f ? __builtin_amdgcn_exp2f(mi[u] - mx) : 0.f;
+            l += f * li[u];
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                if (i + u < a.parts) acc[g] += f * ai[u][g];
+        }
+        m = mx;
+    }
+    const float inv = 1.f / l;
+    const int qrow = tr.q0 + wave * 32 + l32;
+    if (qrow >= tr.q1) return;
+    const int64_t orow = bat * a.o_sb + head * a.o_sh + qrow * a.o_st + 32 * d + 4 * hw;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const f32x4_t w = acc[g] * inv;
+        if constexpr (OF32) {
+            *reinterpret_cast<f32x4_t*>(static_cast<float*>(a.o) + orow + 8 * g) = w;
+        } else {
+            bf16x4_t h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = static_cast<__bf16>(w[e]);
+            *reinterpret_cast<bf16x4_t*>(static_cast<__bf16*>(a.o) + orow + 8 * g) = h;
+        }
+    }
+    if (a.lse != nullptr && d == 0 && hw == 0)
+        a.lse[(static_cast<int64_t>(bat) * a.H + head) * a.Lq + qrow] = (m + __log2f(l)) * 0.69314718055994530942f;
 }
 
 // ----------------------------------------------------------------------------
@@ -894,22 +1010,29 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
     }
 }
 
+template <int D, bool VT, bool OF32>
+void launch_bf16(const AttnArgs& a, hipStream_t s) {
+    const int split = a.n_qtiles * a.B * a.H - a.n_whole;
+    const dim3 grid(a.n_whole + split * a.parts);
+    hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, VT, OF32>), grid, dim3(kBf16Threads), 0, s, a);
+    if (split > 0)
+        hipLaunchKernelGGL((attn_merge_kernel<D, OF32>), dim3(split * (kTileRowsBf16 / 32) * (D / 32)), dim3(64), 0, s, a);
+}
 template <int D, bool VT>
-void launch_bf16_out(const AttnArgs& a, dim3 grid, dim3 block, hipStream_t s) {
-    if (a.o_f32) hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, VT, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, VT, false>), grid, block, 0, s, a);
+void launch_bf16_out(const AttnArgs& a, hipStream_t s) {
+    if (a.o_f32) launch_bf16<D, VT, true>(a, s);
+    else launch_bf16<D, VT, false>(a, s);
 }
 
 }  // namespace
 
 hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, hipStream_t s) {
-    const dim3 grid(a.n_qtiles * a.B * a.H), block(kBf16Threads);
     if (head_dim == 128) {
-        if (a.v_blocked) launch_bf16_out<128, true>(a, grid, block, s);
-        else launch_bf16_out<128, false>(a, grid, block, s);
+        if (a.v_blocked) launch_bf16_out<128, true>(a, s);
+        else launch_bf16_out<128, false>(a, s);
     } else if (head_dim == 64) {
-        if (a.v_blocked) launch_bf16_out<64, true>(a, grid, block, s);
-        else launch_bf16_out<64, false>(a, grid, block, s);
+        if (a.v_blocked) launch_bf16_out<64, true>(a, s);
+        else launch_bf16_out<64, false>(a, s);
     } else {
         return hipErrorInvalidValue;
     }

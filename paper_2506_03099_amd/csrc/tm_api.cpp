@@ -408,12 +408,106 @@ int64_t tm_allowed_pairs(const tm_attn_desc* desc, int32_t q_chunk, const tm_kv_
 
 namespace {
 
+// Query tiles and key tiles of a forward call (a->B, H and Lq are set).
+tm_status plan_tiles(const Geo& g, const Plan& p, tmk::AttnArgs* out) {
+    tmk::AttnArgs& a = *out;
+    a.mode = p.mode;
+    int64_t most_keys = 0;  // keys of the query row that sees the most
+    if (p.mode == 0) {
+        if (p.ranges.size() > size_t(tmk::kMaxRanges))
+            return fail(TM_E_SHAPE, "too many key ranges (%zu)", p.ranges.size());
+        a.n_ranges = int32_t(p.ranges.size());
+        for (size_t i = 0; i < p.ranges.size(); ++i) {
+            a.range_begin[i] = int32_t(p.ranges[i].first);
+            a.range_end[i] = int32_t(p.ranges[i].second);
+            a.n_ktiles += int32_t(ceil_div(p.ranges[i].second - p.ranges[i].first, tmk::kKeyTile));
+        }
+        most_keys = range_len(p.ranges);
+    } else {
+        a.ref_tok = int32_t(std::min(g.RT, p.seq_len));
+        a.chunk_tok = int32_t(g.CT);
+        a.window = int32_t(g.W);
+        a.seq_len = int32_t(p.seq_len);
+        most_keys = std::min(p.seq_len, g.RT + (g.W + 1) * g.CT);
+    }
+    // Query tiles of at most BM rows per (batch, head); tiles never straddle a chunk.
+    auto count_tiles = [&](int64_t BM) {
+        if (p.mode == 0) return ceil_div(p.Lq, BM);
+        const int64_t L = p.seq_len, nc = n_chunks(g, L);
+        int64_t tiles = ceil_div(a.ref_tok, BM);
+        if (nc >= 2) {
+            tiles += (nc - 2) * ceil_div(g.CT, BM);
+            tiles += ceil_div(chunk_end(g, nc - 1, L) - chunk_start(g, nc - 1), BM);
+        }
+        return tiles;
+    };
+    int64_t BM = tmk::kTileRowsBf16;
+    if (g.dtype == TM_F32) {
+        // Key groups: up to 4 until there are four waves per SIMD (2 fit at a
+        // time; shorter waves leave a shorter tail: 24 heads of 2304 rows at
+        // head_dim 64 take 179 us with 4 groups, 202 with 2), 8 only where
+        // that still is at most two waves per SIMD (16 heads of 903 rows: 110
+        // us with 8, 99 with 4; one head of 2304 rows: 36 with 8, 39 with 4),
+        // and no more than there are 32-key blocks.
+        const int64_t waves = count_tiles(32) * g.B * g.H;
+        int groups = 1;
+        while (groups < 4 && waves * groups < 2 * tmk::kF32FillWaves && int64_t(groups) * 64 <= most_keys)
+            groups *= 2;
+        if (g.D == 64 && groups == 4 && waves * 8 <= tmk::kF32FillWaves && 8 * 32 <= most_keys) groups = 8;
+        a.key_groups = groups;
+        BM = tmk::f32_tile_rows(groups);
+    }
+    if (p.mode == 1) {
+        a.ref_tiles = int32_t(ceil_div(a.ref_tok, BM));
+        a.chunk_tiles = int32_t(ceil_div(g.CT, BM));
+    }
+    const int64_t tiles = count_tiles(BM);
+    if (tiles * g.B * g.H > INT32_MAX) return fail(TM_E_SHAPE, "grid too large");
+    a.n_qtiles = int32_t(tiles);
+    return TM_OK;
+}
+
+// Key split of a planned bf16 forward. A workgroup fills a CU, takes about 9 us
+// besides its key loop and 1.1 us per key tile (1.6 with the whole chip busy,
+// whose clock drops), so a split pays where the last round of workgroups leaves
+// half the CUs idle: 480p chunk (171 key tiles) with 1, 3, 5 heads: 205, 208,
+// 200 us whole, 45, 87, 128 split; 40-head reference frame (280 tiles over 25
+// key tiles): 90 -> 69. With more than half a round left over (8 heads, 152
+// tiles) one extra part for some tiles only lengthens the round. A part
+// gets at least 4 key tiles (with 2 the merge costs more than the parts save:
+// reference frame +3 us), and the split has to shorten a tile by 10.
+tmk::AttnSplit plan_split(const Geo& g, const Plan& p, const tmk::AttnArgs& a) {
+    tmk::AttnSplit sp;
+    const int64_t tiles = int64_t(a.n_qtiles) * g.B * g.H;
+    sp.whole = tiles;
+    if (g.dtype != TM_BF16) return sp;
+    // Tiles beyond the last full round of one workgroup per CU. Those of a
+    // whole sequence take unequal times (the heavy ones first), so its last
+    // round is left alone unless it is the only one.
+    const int64_t rest = p.mode == 0 || tiles < tmk::kCUs ? tiles % tmk::kCUs : 0;
+    if (rest == 0) return sp;
+    const int64_t keys = p.mode == 0 ? a.n_ktiles
+                                     : ceil_div(std::min(p.seq_len, g.RT + (g.W + 1) * g.CT), tmk::kKeyTile);
+    const int64_t parts = std::min<int64_t>({tmk::kCUs / rest, keys / 4, 16});
+    if (parts < 2 || keys - ceil_div(keys, parts) < 10) return sp;
+    sp.whole = tiles - rest;
+    sp.parts = int(parts);
+    return sp;
+}
+
+size_t split_bytes(const Geo& g, const tmk::AttnArgs& a, const tmk::AttnSplit& sp) {
+    const int64_t split = int64_t(a.n_qtiles) * g.B * g.H - sp.whole;
+    return size_t(split) * size_t(sp.parts) * (tmk::kTileRowsBf16 / 32) * size_t(tmk::part_floats(int(g.D))) *
+           sizeof(float);
+}
+
 // The forward of both output types: o holds elements of the descriptor's
 // dtype, or fp32 when o_f32 is set (for bf16 inputs the values before the
 // final rounding; for fp32 inputs the same call).
 tm_status attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
                    const tm_kv_cache* cache, const void* k, const void* v, int32_t n_frames,
-                   void* o, bool o_f32, float* lse, hipStream_t stream) {
+                   void* o, bool o_f32, float* lse, void* workspace, size_t workspace_bytes,
+                   hipStream_t stream) {
     Geo g;
     Plan p;
     tm_status st = make_plan(desc, q_chunk, cache, n_frames, &g, &p);
@@ -469,59 +563,24 @@ tm_status attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
     a.H = int32_t(g.H);
     a.Lq = int32_t(p.Lq);
     a.scale_log2 = float(double(g.scale) * 1.4426950408889634);
-    a.mode = p.mode;
-    int64_t most_keys = 0;  // keys of the query row that sees the most
-    if (p.mode == 0) {
-        if (p.ranges.size() > size_t(tmk::kMaxRanges))
-            return fail(TM_E_SHAPE, "too many key ranges (%zu)", p.ranges.size());
-        a.n_ranges = int32_t(p.ranges.size());
-        for (size_t i = 0; i < p.ranges.size(); ++i) {
-            a.range_begin[i] = int32_t(p.ranges[i].first);
-            a.range_end[i] = int32_t(p.ranges[i].second);
-            a.n_ktiles += int32_t(ceil_div(p.ranges[i].second - p.ranges[i].first, tmk::kKeyTile));
+    if ((st = plan_tiles(g, p, &a)) != TM_OK) return st;
+    a.n_whole = a.n_qtiles * a.B * a.H;
+    a.parts = 1;
+    if (workspace != nullptr) {
+        // A workspace that is too small is not used.
+        const tmk::AttnSplit sp = plan_split(g, p, a);
+        const size_t need = split_bytes(g, a, sp);
+        if (need > 0 && need <= workspace_bytes) {
+            if ((st = check_ptr(workspace, need, "workspace")) != TM_OK) return st;
+            if (overlaps(workspace, need, q, q_bytes) || overlaps(workspace, need, o, o_bytes) ||
+                overlaps(workspace, need, a.k, kv_bytes) || overlaps(workspace, need, a.v, kv_bytes) ||
+                (lse != nullptr && overlaps(workspace, need, lse, lse_bytes)))
+                return fail(TM_E_ARG, "workspace overlaps another tensor");
+            a.n_whole = int32_t(sp.whole);
+            a.parts = sp.parts;
+            a.part = static_cast<float*>(workspace);
         }
-        most_keys = range_len(p.ranges);
-    } else {
-        a.ref_tok = int32_t(std::min(g.RT, p.seq_len));
-        a.chunk_tok = int32_t(g.CT);
-        a.window = int32_t(g.W);
-        a.seq_len = int32_t(p.seq_len);
-        most_keys = std::min(p.seq_len, g.RT + (g.W + 1) * g.CT);
     }
-    // Query tiles of at most BM rows per (batch, head); tiles never straddle a chunk.
-    auto count_tiles = [&](int64_t BM) {
-        if (p.mode == 0) return ceil_div(p.Lq, BM);
-        const int64_t L = p.seq_len, nc = n_chunks(g, L);
-        int64_t tiles = ceil_div(a.ref_tok, BM);
-        if (nc >= 2) {
-            tiles += (nc - 2) * ceil_div(g.CT, BM);
-            tiles += ceil_div(chunk_end(g, nc - 1, L) - chunk_start(g, nc - 1), BM);
-        }
-        return tiles;
-    };
-    int64_t BM = tmk::kTileRowsBf16;
-    if (g.dtype == TM_F32) {
-        // Key groups: up to 4 until there are four waves per SIMD (2 fit at a
-        // time; shorter waves leave a shorter tail: 24 heads of 2304 rows at
-        // head_dim 64 take 179 us with 4 groups, 202 with 2), 8 only where
-        // that still is at most two waves per SIMD (16 heads of 903 rows: 110
-        // us with 8, 99 with 4; one head of 2304 rows: 36 with 8, 39 with 4),
-        // and no more than there are 32-key blocks.
-        const int64_t waves = count_tiles(32) * g.B * g.H;
-        int groups = 1;
-        while (groups < 4 && waves * groups < 2 * tmk::kF32FillWaves && int64_t(groups) * 64 <= most_keys)
-            groups *= 2;
-        if (g.D == 64 && groups == 4 && waves * 8 <= tmk::kF32FillWaves && 8 * 32 <= most_keys) groups = 8;
-        a.key_groups = groups;
-        BM = tmk::f32_tile_rows(groups);
-    }
-    if (p.mode == 1) {
-        a.ref_tiles = int32_t(ceil_div(a.ref_tok, BM));
-        a.chunk_tiles = int32_t(ceil_div(g.CT, BM));
-    }
-    const int64_t tiles = count_tiles(BM);
-    if (tiles * g.B * g.H > INT32_MAX) return fail(TM_E_SHAPE, "grid too large");
-    a.n_qtiles = int32_t(tiles);
 
     const hipError_t e = g.dtype == TM_BF16 ? tmk::launch_attn_bf16(a, int(g.D), stream)
                                             : tmk::launch_attn_f32(a, int(g.D), stream);
@@ -536,14 +595,31 @@ extern "C" {
 tm_status tm_sparse_causal_attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
                                     const tm_kv_cache* cache, const void* k, const void* v,
                                     int32_t n_frames, void* o, float* lse, hipStream_t stream) {
-    return attn_fwd(desc, q, q_chunk, cache, k, v, n_frames, o, false, lse, stream);
+    return attn_fwd(desc, q, q_chunk, cache, k, v, n_frames, o, false, lse, nullptr, 0, stream);
 }
 
 tm_status tm_sparse_causal_attn_fwd_f32out(const tm_attn_desc* desc, const void* q,
                                            int32_t q_chunk, const tm_kv_cache* cache,
                                            const void* k, const void* v, int32_t n_frames,
                                            float* o, float* lse, hipStream_t stream) {
-    return attn_fwd(desc, q, q_chunk, cache, k, v, n_frames, o, true, lse, stream);
+    return attn_fwd(desc, q, q_chunk, cache, k, v, n_frames, o, true, lse, nullptr, 0, stream);
+}
+
+size_t tm_sparse_causal_attn_fwd_workspace(const tm_attn_desc* desc, int32_t q_chunk,
+                                           const tm_kv_cache* cache, int32_t n_frames) {
+    Geo g;
+    Plan p;
+    tmk::AttnArgs a{};
+    if (make_plan(desc, q_chunk, cache, n_frames, &g, &p) != TM_OK || plan_tiles(g, p, &a) != TM_OK) return 0;
+    return split_bytes(g, a, plan_split(g, p, a));
+}
+
+tm_status tm_sparse_causal_attn_fwd_ws(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
+                                       const tm_kv_cache* cache, const void* k, const void* v,
+                                       int32_t n_frames, void* o, int32_t o_f32, float* lse,
+                                       void* workspace, size_t workspace_bytes, hipStream_t stream) {
+    return attn_fwd(desc, q, q_chunk, cache, k, v, n_frames, o, o_f32 != 0, lse, workspace,
+                    workspace_bytes, stream);
 }
 
 }  // extern "C"

@@ -14,6 +14,20 @@ constexpr int kMaxRanges = 16;  // key ranges of one query segment (>= TM_MAX_WI
 // tiles per chunk.
 constexpr int kTileRowsBf16 = 256;
 constexpr int kKeyTile = 64;  // keys per tile of the bf16 kernel
+constexpr int kCUs = 256;     // compute units of the target; one bf16 workgroup on each at a time
+
+// Partial result of one wave (32 query rows) over a share of the keys: O in
+// the MFMA layout, then each row's running max and row sum, in floats.
+__host__ __device__ constexpr int64_t part_floats(int head_dim) { return 32 * int64_t(head_dim) + 128; }
+
+// Key split of the query tiles that do not fill a whole round of the chip's
+// CUs: `whole` tiles (a multiple of kCUs) run over all their keys, each of the
+// others is shared out over `parts` workgroups, whose partial results a second
+// kernel merges. parts = 1: no split.
+struct AttnSplit {
+    int64_t whole = 0;
+    int parts = 1;
+};
 
 // The fp32 kernel's workgroups have 4 waves (8 with 8 key groups, head_dim 64
 // only), 32 query rows each; the waves are shared out between key groups and
@@ -51,6 +65,9 @@ struct AttnArgs {
     float scale_log2;  // softmax scale * log2(e)
     int32_t n_qtiles;  // query tiles per (batch, head)
     int32_t key_groups;  // fp32 kernel: shares of a tile's keys (1, 2, 4 or 8)
+    int32_t n_whole;     // bf16 kernel: tiles (of all heads) that are not split
+    int32_t parts;       // bf16 kernel: workgroups per split tile (1: none is split)
+    float* part;         // bf16 kernel: [split tile][part][wave][part_floats]
     // mode 0: every query row of the buffer belongs to one chunk and sees the
     //         same key ranges (streaming form, or one chunk of a sequence);
     // mode 1: the buffer holds a whole sequence (row i = position i); each

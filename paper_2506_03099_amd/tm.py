@@ -104,6 +104,11 @@ def lib() -> ctypes.CDLL:
                                                          ctypes.c_int32, P, P, P]),
             "tm_sparse_causal_attn_fwd_f32out": (ctypes.c_int, [D, P, ctypes.c_int32, P, P, P,
                                                                 ctypes.c_int32, P, P, P]),
+            "tm_sparse_causal_attn_fwd_workspace": (ctypes.c_size_t, [D, ctypes.c_int32, P,
+                                                                      ctypes.c_int32]),
+            "tm_sparse_causal_attn_fwd_ws": (ctypes.c_int, [D, P, ctypes.c_int32, P, P, P,
+                                                            ctypes.c_int32, P, ctypes.c_int32, P, P,
+                                                            ctypes.c_size_t, P]),
             "tm_allowed_pairs": (ctypes.c_int64, [D, ctypes.c_int32, P, ctypes.c_int32]),
             "tm_audio_cross_attn_fwd": (ctypes.c_int, [AD, P, ctypes.c_int32, ctypes.c_int32, P, P,
                                                        P, P, P]),
@@ -154,9 +159,13 @@ def _ptr(t):
     return t.data_ptr()
 
 
+def _current_stream() -> int:
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return _current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
 
@@ -240,17 +249,42 @@ def tm_qkv_produce(cache: KVCache, chunk: int, q, k, v, q_gain=None, k_gain=None
     return q_out
 
 
+def _workspace(nbytes: int, device, stream: int):
+    """A workspace for one call on `stream`: memory of torch's allocator, which
+    hands it out again in the order of the current stream once the call has
+    returned. None (the call then runs without) where that order does not cover
+    the call: another stream than the current one, or a stream under capture;
+    and where the memory is not to be had."""
+    if nbytes == 0 or stream != _current_stream() or torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
+def _fwd(desc, q, q_chunk, cache, k, v, n_frames, o, o_f32, lse, stream):
+    h = cache.handle if cache is not None else None
+    d = ctypes.byref(desc)
+    L = lib()
+    stream = _stream(stream)
+    ws, n = None, 0
+    if desc.dtype == TM_BF16:
+        n = L.tm_sparse_causal_attn_fwd_workspace(d, q_chunk, h, n_frames)
+        if n:
+            ws = _workspace(n, q.device, stream)
+    _check(L.tm_sparse_causal_attn_fwd_ws(d, _ptr(q), q_chunk, h, _ptr(k), _ptr(v), n_frames, _ptr(o),
+                                          o_f32, _ptr(lse), _ptr(ws), n, stream))
+    return o
+
+
 def tm_sparse_causal_attn_fwd(desc: tm_attn_desc, q, q_chunk: int, cache: KVCache | None = None,
                               k=None, v=None, n_frames: int = 0, o=None, lse=None,
                               stream=None):
     """Sparse causal attention; returns ``o`` (allocated like q if not given)."""
     if o is None:
         o = torch.empty_like(q)
-    h = cache.handle if cache is not None else None
-    _check(lib().tm_sparse_causal_attn_fwd(ctypes.byref(desc), _ptr(q), q_chunk, h, _ptr(k),
-                                           _ptr(v), n_frames, _ptr(o), _ptr(lse),
-                                           _stream(stream)))
-    return o
+    return _fwd(desc, q, q_chunk, cache, k, v, n_frames, o, 0, lse, stream)
 
 
 def tm_sparse_causal_attn_fwd_f32out(desc: tm_attn_desc, q, q_chunk: int,
@@ -260,11 +294,7 @@ def tm_sparse_causal_attn_fwd_f32out(desc: tm_attn_desc, q, q_chunk: int,
     if not given); returns ``o``."""
     if o is None:
         o = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    h = cache.handle if cache is not None else None
-    _check(lib().tm_sparse_causal_attn_fwd_f32out(ctypes.byref(desc), _ptr(q), q_chunk, h, _ptr(k),
-                                                  _ptr(v), n_frames, _ptr(o), _ptr(lse),
-                                                  _stream(stream)))
-    return o
+    return _fwd(desc, q, q_chunk, cache, k, v, n_frames, o, 1, lse, stream)
 
 
 def make_audio_desc(batch, heads, head_dim, tokens_per_frame, audio_per_frame, audio_frames,
