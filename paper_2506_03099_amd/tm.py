@@ -160,7 +160,9 @@ def _ptr(t):
 
 
 def _current_stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # torch.cuda.current_stream() builds a Stream object, 2.6 us of a call that
+    # takes 8; the handle alone takes 0.2
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _stream(stream):
