@@ -227,6 +227,16 @@ tm_status tm_sparse_causal_attn_bwd(const tm_attn_desc* desc, int32_t n_frames, 
                                     const void* dout, float* delta, void* dq, void* dk, void* dv,
                                     hipStream_t stream);
 
+/* The same backward pass with a caller-owned workspace for the call's duration
+ * on `stream`, as in tm_sparse_causal_attn_fwd_ws: tiles that do not fill the
+ * GPU (c_0's keys, which every query sees, above all) then share their sums out
+ * over several workgroups, whose fp32 parts are added up in a fixed order. */
+size_t tm_sparse_causal_attn_bwd_workspace(const tm_attn_desc* desc, int32_t n_frames);
+tm_status tm_sparse_causal_attn_bwd_ws(const tm_attn_desc* desc, int32_t n_frames, const void* q,
+                                       const void* k, const void* v, const void* o, const float* lse,
+                                       const void* dout, float* delta, void* dq, void* dk, void* dv,
+                                       void* workspace, size_t workspace_bytes, hipStream_t stream);
+
 /* The same backward pass without the caller's workspace, for callers that
  * cannot allocate device memory (code under HIP graph capture, serving loops
  * or harnesses that forbid allocation): delta lives in a device-global array

@@ -97,6 +97,46 @@ __device__ __forceinline__ bf16x8_t read_tr(const lds_u8* tile, uint32_t lo, uin
     return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// Stores a wave's 32 rows of D bf16, held as X^T accumulators (register 4*g + e
+// of block d in a lane: row l32, dimension 32*d + 8*g + 4*hw + e), scaled, as
+// whole rows: through 32 * D * 2 bytes of the wave's own LDS (16-byte chunk c
+// of row r at c ^ (r & CM)), so that a store instruction covers whole rows and
+// not 8 bytes of 32 of them. Rows at or past n are not stored.
+template <int D>
+__device__ __forceinline__ void store_rows(lds_u8* rows, const f32x16_t (&acc)[D / 32], float scale,
+                                           __bf16* out, int64_t stride, int n, int lane) {
+    constexpr int ROWB = D * 2, CPR = D / 8, CM = CPR < 16 ? 7 : 15;
+    const int l32 = lane & 31, hw = lane >> 5;
+#pragma unroll
+    for (int d = 0; d < D / 32; ++d) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            bf16x4_t w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(acc[d][4 * g + e] * scale);
+            *(lds_bf16x4_t*)(rows + l32 * ROWB + (((4 * d + g) ^ (l32 & CM)) << 4) + 8 * hw) = w;
+        }
+    }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 32 * CPR / 64; ++i) {
+        const int ch = 64 * i + lane, row = ch / CPR;
+        const f32x4_t w = *(const lds_f32x4_t*)(rows + row * ROWB + (((ch % CPR) ^ (row & CM)) << 4));
+        if (row < n) *reinterpret_cast<f32x4_t*>(out + row * stride + (ch % CPR) * 8) = w;
+    }
+}
+
+// The same accumulators unscaled, in register order: whole KBs per store.
+template <int D>
+__device__ __forceinline__ void store_part(float* part, const f32x16_t (&acc)[D / 32], int lane) {
+#pragma unroll
+    for (int d = 0; d < D / 32; ++d)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f32x4_t*>(part + (4 * d + g) * 256 + 4 * lane) =
+                f32x4_t{acc[d][4 * g], acc[d][4 * g + 1], acc[d][4 * g + 2], acc[d][4 * g + 3]};
+}
+
 // ---------------------------------------------------------------------------
 // delta = rowsum(dO * O): one thread per (batch, token, head) row
 // ---------------------------------------------------------------------------
@@ -203,14 +243,18 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
     // the XCDs and fill the end of the grid.
     const int BH = a.B * a.H;
     const int rest = a.q_tiles - a.q_ref_tiles;
-    const int n_chunk = rest * BH;
-    int bh, t;
+    const int n_chunk = rest * BH * a.q_parts;
+    int bh, t, part;
     if (static_cast<int>(blockIdx.x) < n_chunk) {
-        const int id = xcd_logical_id(blockIdx.x, n_chunk);
+        int id = xcd_logical_id(blockIdx.x, n_chunk);
+        part = id % a.q_parts;
+        id /= a.q_parts;
         bh = id / rest;
         t = a.q_ref_tiles + id % rest;
     } else {
-        const int r = blockIdx.x - n_chunk;
+        int r = blockIdx.x - n_chunk;
+        part = r % a.q_parts;
+        r /= a.q_parts;
         bh = r / a.q_ref_tiles;
         t = r % a.q_ref_tiles;
     }
@@ -228,26 +272,12 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
     const float* lse = a.lse + (static_cast<int64_t>(b) * a.H + h) * a.L;
     const float* dl = a.delta + (static_cast<int64_t>(b) * a.H + h) * a.L;
 
-    // this wave's 32 query rows: Q and dO as the B operands of S^T and dP^T
-    const int qrow = q0 + wave * 32 + l32;
-    const bool row_ok = qrow < q1;
-    const int qr = min(qrow, q1 - 1);
-    bf16x8_t qf[KK], dof[KK];
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-        qf[kk] = *reinterpret_cast<const bf16x8_t*>(qg + qr * st + kk * 16 + hw * 8);
-        dof[kk] = *reinterpret_cast<const bf16x8_t*>(dog + qr * st + kk * 16 + hw * 8);
-    }
-    const float lse2 = lse[qr] * 1.4426950408889634f;
-    const float dlt = dl[qr];
-    const float c = a.scale_log2;
-    // the Q/dO loads land before any direct load is issued
-    wait_lds_dma();
-
     // key tile j of the sequence: first key k0 and end ke of its range
     const Ranges rg = key_ranges(a, chunk);
     const int n0 = (rg.e0 - rg.b0 + BN - 1) / BN;
-    const int nt = n0 + (rg.n == 2 ? (rg.e1 - rg.b1 + BN - 1) / BN : 0);
+    const int tiles = n0 + (rg.n == 2 ? (rg.e1 - rg.b1 + BN - 1) / BN : 0);
+    // this part's tiles [j0, nt) (none where there are fewer tiles than parts)
+    const int j0 = tiles * part / a.q_parts, nt = tiles * (part + 1) / a.q_parts;
     auto tile_at = [&](int j, int& k0, int& ke) __attribute__((always_inline)) {
         if (j < n0) {
             k0 = rg.b0 + j * BN;
@@ -277,6 +307,21 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
         }
     };
 
+    // the first tile's loads, and behind them this wave's operands: both
+    // latencies pass together
+    if (j0 < nt) issue(j0, 0);
+    // this wave's 32 query rows: Q and dO as the B operands of S^T and dP^T
+    const int qrow = q0 + wave * 32 + l32;
+    const int qr = min(qrow, q1 - 1);
+    bf16x8_t qf[KK], dof[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+        qf[kk] = *reinterpret_cast<const bf16x8_t*>(qg + qr * st + kk * 16 + hw * 8);
+        dof[kk] = *reinterpret_cast<const bf16x8_t*>(dog + qr * st + kk * 16 + hw * 8);
+    }
+    const float lse2 = lse[qr] * 1.4426950408889634f;
+    const float dlt = dl[qr];
+    const float c = a.scale_log2;
     const TileBases<D> tb(lane);
     f32x16_t acc[DB];
 #pragma unroll
@@ -329,10 +374,9 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
         }
     };
 
-    issue(0, 0);
     wait_lds_dma();
     __syncthreads();
-    for (int j = 0; j < nt; j += 2) {
+    for (int j = j0; j < nt; j += 2) {
         // buffer 1 was last read in the previous tile, before the barrier
         if (j + 1 < nt) issue(j + 1, 1);
         compute(std::integral_constant<int, 0>{}, j);
@@ -345,18 +389,15 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
         __syncthreads();
     }
 
-    if (row_ok) {
-        __bf16* dq = static_cast<__bf16*>(a.dq) + base + qrow * st;
-        const float sc = a.scale;
-#pragma unroll
-        for (int d = 0; d < DB; ++d) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                bf16x4_t w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(acc[d][4 * g + e] * sc);
-                *reinterpret_cast<bf16x4_t*>(dq + 32 * d + 8 * g + 4 * hw) = w;
-            }
+    // (every wave is past the last tile's barrier: the LDS is free)
+    const int w0 = q0 + wave * 32;
+    if (w0 < q1) {
+        if (a.q_parts > 1) {
+            const int64_t at = ((static_cast<int64_t>(bh) * a.q_tiles + t) * a.q_parts + part) * NW + wave;
+            store_part<D>(a.dq_part + at * (32 * D), acc, lane);
+        } else {
+            store_rows<D>(L + wave * 32 * ROWB, acc, a.scale, static_cast<__bf16*>(a.dq) + base + w0 * st, st,
+                          q1 - w0, lane);
         }
     }
 }
@@ -398,14 +439,24 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
     // all of them); the chunks' tiles after them, grouped per XCD so that a
     // head's tiles share an L2.
     const int BH = a.B * a.H;
-    const int n_ref = a.k_ref_tiles * BH;
-    int bh, t;
+    const int n_ref = a.k_ref_tiles * BH * a.k_ref_parts;
+    int bh, t, part, parts;
+    int64_t slot = 0;  // of this part's sums
     if (static_cast<int>(blockIdx.x) < n_ref) {
-        bh = blockIdx.x / a.k_ref_tiles;
-        t = blockIdx.x % a.k_ref_tiles;
+        parts = a.k_ref_parts;
+        slot = blockIdx.x;
+        int r = blockIdx.x;
+        part = r % parts;
+        r /= parts;
+        bh = r / a.k_ref_tiles;
+        t = r % a.k_ref_tiles;
     } else {
         const int rest = a.k_tiles - a.k_ref_tiles;
-        const int id = xcd_logical_id(blockIdx.x - n_ref, rest * BH);
+        parts = a.k_chunk_parts;
+        int id = xcd_logical_id(blockIdx.x - n_ref, rest * BH * parts);
+        slot = (a.k_ref_parts > 1 ? n_ref : 0) + id;
+        part = id % parts;
+        id /= parts;
         bh = id / rest;
         t = a.k_ref_tiles + id % rest;
     }
@@ -421,6 +472,14 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
     } else {
         qbeg = a.ref_tok + (chunk - 1) * a.chunk_tok;
         qend = min(a.ref_tok + (chunk + a.window) * a.chunk_tok, a.L);
+    }
+    // this part's 32-query stages (none where there are fewer stages than parts)
+    int n_st = (qend - qbeg + BQ - 1) / BQ;
+    {
+        const int s0 = n_st * part / parts, s1 = n_st * (part + 1) / parts;
+        qend = min(qbeg + s1 * BQ, qend);
+        qbeg += s0 * BQ;
+        n_st = s1 - s0;
     }
 
     const int64_t st = static_cast<int64_t>(a.H) * D;
@@ -458,6 +517,8 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
         }
     };
 
+    // the first stage's loads; the K and V rows' latency passes with theirs
+    if (n_st > 0) issue(qbeg, 0);
     // this wave's keys: k0 + 32 * wave + l32
     const int kw = k0 + 32 * wave;
     const bool busy = kw < k1;
@@ -487,9 +548,6 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
             lds_dma16x2(vs, vo[0], l, vs, vo[1], l + 1024);
         }
     }
-    // the K loads and the V rows land before any stage load is issued
-    wait_lds_dma();
-
     const TileBases<D> tb(lane);
     f32x16_t dk[DB], dv[DB];
 #pragma unroll
@@ -567,8 +625,6 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
             __syncthreads();
         }
     };
-    const int n_st = (qend - qbeg + BQ - 1) / BQ;
-    issue(qbeg, 0);
     wait_lds_dma();
     __syncthreads();
     for (int ts = 0; ts < n_st; ts += 2) {
@@ -586,40 +642,120 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
         __syncthreads();
     }
 
-    const float sc = a.scale;
-    const int key = kw + l32;
-    if (key < k1) {
-        __bf16* dkp = static_cast<__bf16*>(a.dk) + base + key * st;
-        __bf16* dvp = static_cast<__bf16*>(a.dv) + base + key * st;
-#pragma unroll
-        for (int d = 0; d < DB; ++d) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                bf16x4_t wk, wv;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    wk[e] = static_cast<__bf16>(dk[d][4 * q + e] * sc);
-                    wv[e] = static_cast<__bf16>(dv[d][4 * q + e]);
-                }
-                *reinterpret_cast<bf16x4_t*>(dkp + 32 * d + 8 * q + 4 * hw) = wk;
-                *reinterpret_cast<bf16x4_t*>(dvp + 32 * d + 8 * q + 4 * hw) = wv;
-            }
+    // (every wave is past the last stage's barrier: the stage buffers are free)
+    if (busy) {
+        if (parts > 1) {
+            float* const p = a.dkdv_part + (slot * NW + wave) * (2 * 32 * D);
+            store_part<D>(p, dk, lane);
+            store_part<D>(p + 32 * D, dv, lane);
+        } else {
+            lds_u8* const rows = L + wave * 32 * ROWB;
+            store_rows<D>(rows, dk, a.scale, static_cast<__bf16*>(a.dk) + base + kw * st, st, k1 - kw, lane);
+            asm volatile("" ::: "memory");
+            store_rows<D>(rows, dv, 1.f, static_cast<__bf16*>(a.dv) + base + kw * st, st, k1 - kw, lane);
         }
+    }
+}
+
+// Adds up the parts of split tiles, in order: one wave per 32 rows and 32
+// dimensions of one tensor. Blocks [0, n_q) take the query tiles' dQ (where
+// split), then the split key tiles' dK and dV.
+template <int D>
+__global__ __launch_bounds__(64) void bwd_sum_kernel(const BwdArgs a, int n_q) {
+    constexpr int DB = D / 32, NW = 4, U = 4;
+    const int lane = threadIdx.x, hw = lane >> 5, l32 = lane & 31;
+    int i = blockIdx.x;
+    const bool is_q = i < n_q;
+    if (!is_q) i -= n_q;
+    const int d = i % DB;
+    i /= DB;
+    const int tensor = is_q ? 0 : i % 2;
+    if (!is_q) i /= 2;
+    const int wave = i % NW;
+    i /= NW;  // split tile
+    const int BH = a.B * a.H;
+    int bh, t, parts, chunk, r0, r1;
+    const float* p;
+    int64_t step;  // from part to part
+    __bf16* out;
+    if (is_q) {
+        parts = a.q_parts;
+        bh = i / a.q_tiles;
+        t = i % a.q_tiles;
+        tile_rows(a, t, kBwdQTile, a.q_ref_tiles, a.q_chunk_tiles, chunk, r0, r1);
+        step = NW * 32 * D;
+        p = a.dq_part + (static_cast<int64_t>(i) * parts * NW + wave) * (32 * D);
+        out = static_cast<__bf16*>(a.dq);
+    } else {
+        const int ref = a.k_ref_parts > 1 ? a.k_ref_tiles * BH : 0;
+        int64_t slot;
+        if (i < ref) {
+            parts = a.k_ref_parts;
+            slot = static_cast<int64_t>(i) * parts;
+            bh = i / a.k_ref_tiles;
+            t = i % a.k_ref_tiles;
+        } else {
+            const int rest = a.k_tiles - a.k_ref_tiles;
+            parts = a.k_chunk_parts;
+            slot = static_cast<int64_t>(ref) * a.k_ref_parts + static_cast<int64_t>(i - ref) * parts;
+            bh = (i - ref) / rest;
+            t = a.k_ref_tiles + (i - ref) % rest;
+        }
+        tile_rows(a, t, kBwdKTile, a.k_ref_tiles, a.k_chunk_tiles, chunk, r0, r1);
+        step = NW * 2 * 32 * D;
+        p = a.dkdv_part + (slot * NW + wave) * (2 * 32 * D) + tensor * (32 * D);
+        out = static_cast<__bf16*>(tensor == 0 ? a.dk : a.dv);
+    }
+    const int row = r0 + 32 * wave + l32;
+    if (r0 + 32 * wave >= r1) return;
+    p += 4 * d * 256 + 4 * lane;
+    f32x4_t acc[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[g] = f32x4_t{};
+    for (int j = 0; j < parts; j += U) {
+        f32x4_t x[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                x[u][g] = *reinterpret_cast<const f32x4_t*>(p + min(j + u, parts - 1) * step + g * 256);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j + u < parts) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) acc[g] += x[u][g];
+            }
+    }
+    if (row >= r1) return;
+    const float sc = tensor == 0 ? a.scale : 1.f;
+    out += ((static_cast<int64_t>(bh / a.H) * a.L + row) * a.H + bh % a.H) * D + 32 * d + 4 * hw;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        bf16x4_t w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(acc[g][e] * sc);
+        *reinterpret_cast<bf16x4_t*>(out + 8 * g) = w;
     }
 }
 
 template <int D>
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t s) {
-    const int64_t rows = static_cast<int64_t>(a.B) * a.L * a.H;
-    const int64_t g0 = (rows + 255) / 256;
-    const int64_t g1 = static_cast<int64_t>(a.q_tiles) * a.B * a.H;
-    const int64_t g2 = static_cast<int64_t>(a.k_tiles) * a.B * a.H;
-    if (g0 > INT32_MAX || g1 > INT32_MAX || g2 > INT32_MAX) return hipErrorInvalidValue;
+    const int64_t bh = static_cast<int64_t>(a.B) * a.H;
+    const int64_t g0 = (bh * a.L + 255) / 256;
+    const int64_t g1 = a.q_tiles * bh * a.q_parts;
+    const int64_t rest = a.k_tiles - a.k_ref_tiles;
+    const int64_t g2 = (a.k_ref_tiles * static_cast<int64_t>(a.k_ref_parts) + rest * a.k_chunk_parts) * bh;
+    const int64_t n_q = a.q_parts > 1 ? a.q_tiles * bh * 4 * (D / 32) : 0;
+    const int64_t n_k = ((a.k_ref_parts > 1 ? a.k_ref_tiles : 0) + (a.k_chunk_parts > 1 ? rest : 0)) * bh * 4 * 2 * (D / 32);
+    if (g0 > INT32_MAX || g1 > INT32_MAX || g2 > INT32_MAX || n_q + n_k > INT32_MAX) return hipErrorInvalidValue;
     hipLaunchKernelGGL(bwd_delta_kernel<D>, dim3(static_cast<unsigned>(g0)), dim3(256), 0, s,
                        static_cast<const __bf16*>(a.o), static_cast<const __bf16*>(a.dout), a.delta,
                        a.B, a.L, a.H);
     hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(static_cast<unsigned>(g1)), dim3(kDqThreads), 0, s, a);
     hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3(static_cast<unsigned>(g2)), dim3(kDkdvThreads), 0, s, a);
+    if (n_q + n_k > 0)
+        hipLaunchKernelGGL(bwd_sum_kernel<D>, dim3(static_cast<unsigned>(n_q + n_k)), dim3(64), 0, s, a,
+                           static_cast<int>(n_q));
     return hipGetLastError();
 }
 

@@ -626,11 +626,70 @@ tm_status tm_sparse_causal_attn_fwd_ws(const tm_attn_desc* desc, const void* q, 
 
 namespace {
 
+// Query and key tiles of a backward call over L tokens.
+tm_status plan_bwd_tiles(const Geo& g, int64_t L, tmk::BwdArgs* a) {
+    const int64_t nc = n_chunks(g, L);
+    const int64_t ref_rows = std::min(g.RT, L);
+    const int64_t qrt = ceil_div(ref_rows, tmk::kBwdQTile), qct = ceil_div(g.CT, tmk::kBwdQTile);
+    const int64_t krt = ceil_div(ref_rows, tmk::kBwdKTile), kct = ceil_div(g.CT, tmk::kBwdKTile);
+    const int64_t q_tiles = qrt + (nc - 1) * qct, k_tiles = krt + (nc - 1) * kct;
+    if (q_tiles * g.B * g.H > INT32_MAX || k_tiles * g.B * g.H > INT32_MAX)
+        return fail(TM_E_SHAPE, "grid too large");
+    a->q_tiles = int32_t(q_tiles);
+    a->q_ref_tiles = int32_t(qrt);
+    a->q_chunk_tiles = int32_t(qct);
+    a->k_tiles = int32_t(k_tiles);
+    a->k_ref_tiles = int32_t(krt);
+    a->k_chunk_tiles = int32_t(kct);
+    return TM_OK;
+}
+
+// Bytes of the partial sums of a split backward.
+struct BwdParts {
+    size_t dkdv = 0, dq = 0;
+    size_t total() const { return dkdv + dq; }
+};
+
+// Parts of the backward's tiles. c_0's key tiles see every query, so with few
+// heads or short sequences they alone run on while the chunks' tiles are long
+// done (21 frames of 256 tokens, 8 heads: 168 stages of 32 queries against 48;
+// dK/dV 180 us whole, 89 with 4 parts each). They are cut to the length of a
+// chunk's tile, or of an evenly filled slot if that is longer (the 480p clip
+// with 40 heads: no split). The chunks' key tiles and the query tiles are split
+// only where all parts still fit the slots at a time (one head of that
+// sequence: 266 -> 80 us forward and backward). A part keeps 8 stages or 6 key
+// tiles, about what its start costs.
+BwdParts plan_bwd_parts(const Geo& g, int64_t L, tmk::BwdArgs* a) {
+    constexpr int64_t kSlots = 2 * tmk::kCUs;  // workgroups of either kernel that run at a time
+    constexpr int64_t kMaxParts = 16;
+    const int64_t BH = g.B * g.H;
+    // dK/dV, in 32-query stages: c_0's key tiles see every query, a chunk's W + 1 chunks.
+    const int64_t n0 = ceil_div(L, 32), n1 = std::min(n0, ceil_div((g.W + 1) * g.CT, 32));
+    const int64_t ref = a->k_ref_tiles * BH, rest = (a->k_tiles - a->k_ref_tiles) * BH;
+    int64_t chunk_parts = 1;
+    if (rest > 0)
+        chunk_parts = std::max<int64_t>(1, std::min({(kSlots - ref) / rest, n1 / 8, kMaxParts}));
+    const int64_t even = (ref * n0 + rest * n1) / kSlots;  // stages of a slot if all were busy
+    const int64_t target = std::max<int64_t>({even, rest > 0 ? n1 / chunk_parts : 0, 8});
+    a->k_chunk_parts = int32_t(chunk_parts);
+    a->k_ref_parts = int32_t(std::max<int64_t>(1, std::min(n0 / target, kMaxParts)));
+    // dQ, in 64-key tiles.
+    const int64_t nq = ceil_div(std::min(L, g.RT + (g.W + 1) * g.CT), 64);
+    a->q_parts = int32_t(std::max<int64_t>(1, std::min({kSlots / (a->q_tiles * BH), nq / 6, kMaxParts})));
+    BwdParts b;
+    const int64_t tile = 4 * 32 * g.D * int64_t(sizeof(float));  // one tensor of a tile
+    b.dkdv = size_t(2 * tile * ((a->k_ref_parts > 1 ? ref * a->k_ref_parts : 0) +
+                                (chunk_parts > 1 ? rest * chunk_parts : 0)));
+    b.dq = a->q_parts > 1 ? size_t(tile * a->q_tiles * BH * a->q_parts) : 0;
+    return b;
+}
+
 // The backward with a caller's delta workspace, or (delta == nullptr) with the
 // library's device-global workspace, which allocates nothing.
 tm_status attn_bwd(const tm_attn_desc* desc, int32_t n_frames, const void* q, const void* k,
                    const void* v, const void* o, const float* lse, const void* dout, float* delta,
-                   void* dq, void* dk, void* dv, hipStream_t stream) {
+                   void* dq, void* dk, void* dv, void* workspace, size_t workspace_bytes,
+                   hipStream_t stream) {
     const bool use_scratch = delta == nullptr;
     Geo g;
     tm_status st = check_desc(desc, &g);
@@ -697,19 +756,28 @@ tm_status attn_bwd(const tm_attn_desc* desc, int32_t n_frames, const void* q, co
     a.window = int32_t(g.W);
     a.scale = g.scale;
     a.scale_log2 = float(double(g.scale) * 1.4426950408889634);
-    const int64_t nc = n_chunks(g, L);
-    const int64_t ref_rows = std::min(g.RT, L);
-    const int64_t qrt = ceil_div(ref_rows, tmk::kBwdQTile), qct = ceil_div(g.CT, tmk::kBwdQTile);
-    const int64_t krt = ceil_div(ref_rows, tmk::kBwdKTile), kct = ceil_div(g.CT, tmk::kBwdKTile);
-    const int64_t q_tiles = qrt + (nc - 1) * qct, k_tiles = krt + (nc - 1) * kct;
-    if (q_tiles * g.B * g.H > INT32_MAX || k_tiles * g.B * g.H > INT32_MAX)
-        return fail(TM_E_SHAPE, "grid too large");
-    a.q_tiles = int32_t(q_tiles);
-    a.q_ref_tiles = int32_t(qrt);
-    a.q_chunk_tiles = int32_t(qct);
-    a.k_tiles = int32_t(k_tiles);
-    a.k_ref_tiles = int32_t(krt);
-    a.k_chunk_tiles = int32_t(kct);
+    if ((st = plan_bwd_tiles(g, L, &a)) != TM_OK) return st;
+    a.k_ref_parts = a.k_chunk_parts = a.q_parts = 1;
+    if (workspace != nullptr) {
+        // A workspace that is too small is not used.
+        tmk::BwdArgs sp = a;
+        const BwdParts need = plan_bwd_parts(g, L, &sp);
+        if (need.total() > 0 && need.total() <= workspace_bytes) {
+            if ((st = check_ptr(workspace, need.total(), "workspace")) != TM_OK) return st;
+            for (int j = 0; j < 5; ++j)
+                if (overlaps(workspace, need.total(), ins[j], t_bytes))
+                    return fail(TM_E_ARG, "workspace overlaps %s", in_names[j]);
+            for (int j = 0; j < 3; ++j)
+                if (overlaps(workspace, need.total(), outs[j], t_bytes))
+                    return fail(TM_E_ARG, "workspace overlaps %s", out_names[j]);
+            if (overlaps(workspace, need.total(), lse, r_bytes) ||
+                overlaps(workspace, need.total(), delta, r_bytes))
+                return fail(TM_E_ARG, "workspace overlaps lse or delta");
+            sp.dkdv_part = static_cast<float*>(workspace);
+            sp.dq_part = reinterpret_cast<float*>(static_cast<char*>(workspace) + need.dkdv);
+            a = sp;
+        }
+    }
     const hipError_t e = tmk::launch_attn_bwd_bf16(a, int(g.D), stream);
     if (e != hipSuccess) return fail(TM_E_DEVICE, "backward launch: %s", hipGetErrorString(e));
     return TM_OK;
@@ -724,14 +792,32 @@ tm_status tm_sparse_causal_attn_bwd(const tm_attn_desc* desc, int32_t n_frames, 
                                     const void* dout, float* delta, void* dq, void* dk, void* dv,
                                     hipStream_t stream) {
     if (delta == nullptr) return fail(TM_E_ARG, "delta is NULL");
-    return attn_bwd(desc, n_frames, q, k, v, o, lse, dout, delta, dq, dk, dv, stream);
+    return attn_bwd(desc, n_frames, q, k, v, o, lse, dout, delta, dq, dk, dv, nullptr, 0, stream);
+}
+
+size_t tm_sparse_causal_attn_bwd_workspace(const tm_attn_desc* desc, int32_t n_frames) {
+    Geo g;
+    tmk::BwdArgs a{};
+    if (check_desc(desc, &g) != TM_OK || g.dtype != TM_BF16 || n_frames < 1) return 0;
+    const int64_t L = int64_t(n_frames) * g.T;
+    if (L > kMaxTokens || plan_bwd_tiles(g, L, &a) != TM_OK) return 0;
+    return plan_bwd_parts(g, L, &a).total();
+}
+
+tm_status tm_sparse_causal_attn_bwd_ws(const tm_attn_desc* desc, int32_t n_frames, const void* q,
+                                       const void* k, const void* v, const void* o, const float* lse,
+                                       const void* dout, float* delta, void* dq, void* dk, void* dv,
+                                       void* workspace, size_t workspace_bytes, hipStream_t stream) {
+    if (delta == nullptr) return fail(TM_E_ARG, "delta is NULL");
+    return attn_bwd(desc, n_frames, q, k, v, o, lse, dout, delta, dq, dk, dv, workspace,
+                    workspace_bytes, stream);
 }
 
 tm_status tm_sparse_causal_attn_bwd_noalloc(const tm_attn_desc* desc, int32_t n_frames,
                                             const void* q, const void* k, const void* v,
                                             const void* o, const float* lse, const void* dout,
                                             void* dq, void* dk, void* dv, hipStream_t stream) {
-    return attn_bwd(desc, n_frames, q, k, v, o, lse, dout, nullptr, dq, dk, dv, stream);
+    return attn_bwd(desc, n_frames, q, k, v, o, lse, dout, nullptr, dq, dk, dv, nullptr, 0, stream);
 }
 
 }  // extern "C"

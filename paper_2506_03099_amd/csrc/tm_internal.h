@@ -175,6 +175,12 @@ struct BwdArgs {
     float scale, scale_log2;
     int32_t q_tiles, q_ref_tiles, q_chunk_tiles;
     int32_t k_tiles, k_ref_tiles, k_chunk_tiles;
+    // Workgroups per key tile of c_0 and of the chunks, and per query tile (1:
+    // the tile's own workgroup writes its result; else the partial sums of a
+    // tile's parts, in fp32, are added up by another kernel).
+    int32_t k_ref_parts, k_chunk_parts, q_parts;
+    float* dkdv_part;  // [split key tile][part][wave][dK, dV][32 * D]
+    float* dq_part;    // [query tile][part][wave][32 * D]
 };
 hipError_t launch_attn_bwd_bf16(const BwdArgs& a, int head_dim, hipStream_t s);
 

@@ -116,6 +116,9 @@ def lib() -> ctypes.CDLL:
                                                               ctypes.c_int32, P, P, P, P, P]),
             "tm_sparse_causal_attn_bwd": (ctypes.c_int, [D, ctypes.c_int32, P, P, P, P, P, P, P,
                                                          P, P, P, P]),
+            "tm_sparse_causal_attn_bwd_workspace": (ctypes.c_size_t, [D, ctypes.c_int32]),
+            "tm_sparse_causal_attn_bwd_ws": (ctypes.c_int, [D, ctypes.c_int32, P, P, P, P, P, P, P,
+                                                            P, P, P, P, ctypes.c_size_t, P]),
             "tm_sparse_causal_attn_bwd_noalloc": (ctypes.c_int, [D, ctypes.c_int32, P, P, P, P, P,
                                                                  P, P, P, P, P]),
             "tm_last_error": (ctypes.c_char_p, []),
@@ -346,9 +349,13 @@ def tm_sparse_causal_attn_bwd(desc: tm_attn_desc, n_frames: int, q, k, v, o, lse
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
-    _check(lib().tm_sparse_causal_attn_bwd(ctypes.byref(desc), n_frames, _ptr(q), _ptr(k), _ptr(v),
-                                           _ptr(o), _ptr(lse), _ptr(dout), _ptr(delta), _ptr(dq),
-                                           _ptr(dk), _ptr(dv), _stream(stream)))
+    d = ctypes.byref(desc)
+    stream = _stream(stream)
+    n = lib().tm_sparse_causal_attn_bwd_workspace(d, n_frames)
+    ws = _workspace(n, q.device, stream)
+    _check(lib().tm_sparse_causal_attn_bwd_ws(d, n_frames, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
+                                              _ptr(dout), _ptr(delta), _ptr(dq), _ptr(dk), _ptr(dv),
+                                              _ptr(ws), n, stream))
     return dq, dk, dv
 
 
