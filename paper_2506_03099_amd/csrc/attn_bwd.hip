@@ -138,29 +138,47 @@ __device__ __forceinline__ void store_part(float* part, const f32x16_t (&acc)[D 
 }
 
 // ---------------------------------------------------------------------------
-// delta = rowsum(dO * O): one thread per (batch, token, head) row
+// delta = rowsum(dO * O): D / 8 lanes per (batch, token, head) row, 16 bytes
+// each, one workgroup per head and 64 tokens, so that both tensors are read in
+// whole rows and delta is written in runs of 64 floats. Bound by HBM: 0.68 GB at
+// 480p, 40 heads, 21 frames in 119 us (5.7 TB/s; 174 us with one thread per row).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void bwd_delta_kernel(const __bf16* __restrict__ o,
                                                         const __bf16* __restrict__ dout,
                                                         float* __restrict__ delta, int B, int L,
                                                         int H) {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (idx >= static_cast<int64_t>(B) * L * H) return;
-    const int h = static_cast<int>(idx % H);
-    const int64_t bi = idx / H;  // b * L + i
-    const __bf16* op = o + idx * D;
-    const __bf16* dp = dout + idx * D;
-    float acc = 0.f;
+    constexpr int LPR = D / 8;         // lanes per row
+    constexpr int RPP = 256 / LPR;     // rows per pass
+    constexpr int PASSES = 64 / RPP;
+    __shared__ float sums[64];
+    const int blocks = (L + 63) / 64;
+    // consecutive workgroups take the heads of the same tokens: their rows are
+    // neighbours in memory
+    const int h = blockIdx.x % H;
+    const int rest = blockIdx.x / H;
+    const int t0 = rest % blocks * 64;
+    const int64_t b = rest / blocks;
+    const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
+    bf16x8_t a[PASSES], g[PASSES];
 #pragma unroll
-    for (int c = 0; c < D / 8; ++c) {
-        const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(op + c * 8);
-        const bf16x8_t g = *reinterpret_cast<const bf16x8_t*>(dp + c * 8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc = fmaf(static_cast<float>(a[e]), static_cast<float>(g[e]), acc);
+    for (int i = 0; i < PASSES; ++i) {
+        const int64_t row = (b * L + min(t0 + i * RPP + r0, L - 1)) * H + h;
+        a[i] = *reinterpret_cast<const bf16x8_t*>(o + row * D + c * 8);
+        g[i] = *reinterpret_cast<const bf16x8_t*>(dout + row * D + c * 8);
     }
-    const int64_t b = bi / L, i = bi % L;
-    delta[(b * H + h) * L + i] = acc;
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i) {
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = fmaf(static_cast<float>(a[i][e]), static_cast<float>(g[i][e]), acc);
+#pragma unroll
+        for (int m = 1; m < LPR; m *= 2) acc += __shfl_xor(acc, m);
+        if (c == 0) sums[i * RPP + r0] = acc;
+    }
+    __syncthreads();
+    const int t = t0 + static_cast<int>(threadIdx.x);
+    if (threadIdx.x < 64 && t < L) delta[(b * H + h) * L + t] = sums[threadIdx.x];
 }
 
 // Key ranges of query chunk a: c_0, and chunks max(1, a - W) .. a, merged.
@@ -741,7 +759,7 @@ __global__ __launch_bounds__(64) void bwd_sum_kernel(const BwdArgs a, int n_q) {
 template <int D>
 hipError_t launch_bwd(const BwdArgs& a, hipStream_t s) {
     const int64_t bh = static_cast<int64_t>(a.B) * a.H;
-    const int64_t g0 = (bh * a.L + 255) / 256;
+    const int64_t g0 = static_cast<int64_t>((a.L + 63) / 64) * bh;
     const int64_t g1 = a.q_tiles * bh * a.q_parts;
     const int64_t rest = a.k_tiles - a.k_ref_tiles;
     const int64_t g2 = (a.k_ref_tiles * static_cast<int64_t>(a.k_ref_parts) + rest * a.k_chunk_parts) * bh;
