@@ -64,7 +64,7 @@ typedef __attribute__((address_space(3))) f32x4_t lds_f32x4_t;
 //   row 8*(i/4) + 4*hw + i%4).
 // The chunk is 2*kk + hw or 4*d + cbase, and the swizzle's XOR only touches
 // the chunk bits, so row(kk) = row0 ^ (kk << 5) and tr_lo(d) = tr0 ^ (d << 6):
-// three registers instead of sixteen. pinned() makes a stage derive them anew
+// three registers instead of sixteen. pinned() and at() make a stage derive them anew
 // (one XOR per use) rather than have the compiler keep all of them.
 template <int D>
 struct TileBases {
@@ -80,8 +80,14 @@ struct TileBases {
         tr0 = r * ROWB + ((cbase ^ tr_swizzle<D>(r)) << 4) + half;
         tr8 = r * ROWB + ((cbase ^ tr_swizzle<D>(r + 8)) << 4) + half;
     }
-    __device__ __forceinline__ TileBases pinned() const {
+    __device__ __forceinline__ TileBases pinned() const { return at(0); }
+    // The same in the tile at LDS offset `base` (a multiple of 1 KB, which the
+    // XORs leave alone).
+    __device__ __forceinline__ TileBases at(uint32_t base) const {
         TileBases t = *this;
+        t.row0 += base;
+        t.tr0 += base;
+        t.tr8 += base;
         asm volatile("" : "+v"(t.row0), "+v"(t.tr0), "+v"(t.tr8));
         return t;
     }
@@ -311,12 +317,15 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
         int k0, ke;
         tile_at(j, k0, ke);
         const int last = ke - 1 - k0;
+        // per-lane terms derived anew per tile, not kept (spilled) across it
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
         const void* ks = uniform_ptr(kg + k0 * st);
         const void* vs = uniform_ptr(vg + k0 * st);
 #pragma unroll
         for (int i = 0; i < NBW; ++i) {
             const int blk = i * NW + wave;
-            const int ch = blk * 64 + lane;
+            const int ch = blk * 64 + ln;
             const int row = ch / CPR;
             const int gc = (ch % CPR) ^ tr_swizzle<D>(row);
             const uint32_t voff = static_cast<uint32_t>((min(row, last) * st + gc * 8) * 2);
@@ -345,64 +354,90 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
 #pragma unroll
     for (int d = 0; d < DB; ++d) acc[d] = f32x16_t{};
 
-    // Key tile j from buffer U: S^T = K Q^T and dP^T = V dO^T per 32-key
+    // Key tile j from buffer u: S^T = K Q^T and dP^T = V dO^T per 32-key
     // block kb (register i: key 32*kb + 8*(i/4) + 4*hw + i%4, query l32),
-    // dS^T as the B operand of dQ^T += K^T dS^T (k-step = 16 keys). Only a
-    // range's last tile can hold keys past the range (MASKED).
-    auto tile = [&](auto ucst, auto maskc, int k0, int ke) __attribute__((always_inline)) {
-        constexpr int U = decltype(ucst)::value;
-        constexpr bool MASKED = decltype(maskc)::value;
-        const lds_u8* Ks = L + U * BUF;
-        const lds_u8* Vs = Ks + KT;
-        const TileBases<D> off = tb.pinned();
-        bf16x8_t pf[4];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            f32x16_t s = f32x16_t{}, dp = f32x16_t{};
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                const bf16x8_t kf = *(const lds_bf16x8_t*)(Ks + kb * 32 * ROWB + off.row(kk));
-                const bf16x8_t vf = *(const lds_bf16x8_t*)(Vs + kb * 32 * ROWB + off.row(kk));
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, dof[kk], dp, 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                float p = __builtin_amdgcn_exp2f(fmaf(s[i], c, -lse2));
-                if constexpr (MASKED) p = k0 + 32 * kb + 8 * (i / 4) + 4 * hw + (i % 4) < ke ? p : 0.f;
-                pf[2 * kb + i / 8][i % 8] = static_cast<__bf16>(p * (dp[i] - dlt));
-            }
-        }
-#pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) {
-#pragma unroll
-            for (int d = 0; d < DB; ++d) {
-                const bf16x8_t kt = read_tr<D>(Ks + 16 * j4 * ROWB, off.tr_lo(d), off.tr_hi(d));
-                acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, pf[j4], acc[d], 0, 0, 0);
-            }
-        }
-    };
-    auto compute = [&](auto ucst, int j) __attribute__((always_inline)) {
+    // dS^T as the B operand of dQ^T += K^T dS^T (k-step = 16 keys). Keys past
+    // the range, which only its last tile can hold, get a score of -inf.
+    auto compute = [&](int u, int j) __attribute__((always_inline)) {
         int k0, ke;
         tile_at(j, k0, ke);
-        if (ke - k0 >= BN) {
-            tile(ucst, std::false_type{}, k0, ke);
-        } else {
-            tile(ucst, std::true_type{}, k0, ke);
-        }
+        const lds_u8* Ks = L;
+        const lds_u8* Vs = Ks + KT;
+        const TileBases<D> off = tb.at(u * BUF);
+        // The tile's MFMAs in one order: S(kb 0), dP(0), S(1), dP(1), then dQ,
+        // each preceded by the LDS read of the operand RING MFMAs ahead and
+        // followed by its share of the arithmetic of what is complete by then:
+        // P(0) under dP(0), dS(0) under S(1) and dP(1), P(1) under dP(1), dS(1)
+        // under the first half of dQ (a wave hides its arithmetic under its
+        // own MFMAs, far less under the other wave's). With the arithmetic in
+        // lumps and the accumulators moved between a masked and an unmasked
+        // copy of this body, dQ of the 480p clip took 8.22 ms, now 8.09.
+        constexpr int RING = 4, NS = 4 * KK, NT = NS + 4 * DB;
+        constexpr int EP = 16 / KK;  // elements per step
+        auto frag = [&](int m) __attribute__((always_inline)) {
+            if (m < NS) {
+                const lds_u8* T = (m / KK) % 2 == 0 ? Ks : Vs;
+                return *(const lds_bf16x8_t*)(T + (m / (2 * KK)) * 32 * ROWB + off.row(m % KK));
+            }
+            const int j4 = (m - NS) / DB, d = (m - NS) % DB;
+            return read_tr<D>(Ks + 16 * j4 * ROWB, off.tr_lo(d), off.tr_hi(d));
+        };
+        bf16x8_t pf[4], fr[RING];
+        f32x16_t s[2], dp[2];
+        s[0] = s[1] = dp[0] = dp[1] = f32x16_t{};
+        // P of element i of key block kb, in place of its score; dS from it
+        auto form_p = [&](int kb, int i) __attribute__((always_inline)) {
+            s[kb][i] = __builtin_amdgcn_exp2f(fmaf(s[kb][i], c, -lse2));
+        };
+        auto form_ds = [&](int kb, int i) __attribute__((always_inline)) {
+            pf[2 * kb + i / 8][i % 8] = static_cast<__bf16>(s[kb][i] * (dp[kb][i] - dlt));
+        };
+#pragma unroll
+        for (int m = 0; m < RING; ++m) fr[m] = frag(m);
+        auto step = [&](int m) __attribute__((always_inline)) {
+            const int kb = m / (2 * KK), kk = m % KK;
+            if (m >= NS) {
+                const int j4 = (m - NS) / DB, d = (m - NS) % DB;
+                acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m % RING], pf[j4], acc[d], 0, 0, 0);
+            } else if ((m / KK) % 2 == 0) {
+                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m % RING], qf[kk], s[kb], 0, 0, 0);
+            } else {
+                dp[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m % RING], dof[kk], dp[kb], 0, 0, 0);
+            }
+            if (m + RING < NT) fr[m % RING] = frag(m + RING);
+            if ((m == KK || m == 3 * KK) && k0 + BN > ke) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (k0 + 32 * kb + 8 * (i / 4) + 4 * hw + (i % 4) >= ke) s[kb][i] = kNegInf;
+            }
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int e0 = (m - (2 * b + 1) * KK) * EP;  // P: S(b) is complete
+                const int d0 = (m - (2 * b + 2) * KK) * EP;  // dS: dP(b) is complete
+#pragma unroll
+                for (int e = 0; e < EP; ++e) {
+                    if (e0 + e >= 0 && e0 + e < 16) form_p(b, e0 + e);
+                    if (d0 + e >= 0 && d0 + e < 16) form_ds(b, d0 + e);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // (three loops, as the compiler does not unroll all steps as one)
+#pragma unroll
+        for (int m = 0; m < 2 * KK; ++m) step(m);
+#pragma unroll
+        for (int m = 2 * KK; m < NS; ++m) step(m);
+#pragma unroll
+        for (int m = NS; m < NT; ++m) step(m);
     };
-
     wait_lds_dma();
     __syncthreads();
-    for (int j = j0; j < nt; j += 2) {
-        // buffer 1 was last read in the previous tile, before the barrier
-        if (j + 1 < nt) issue(j + 1, 1);
-        compute(std::integral_constant<int, 0>{}, j);
-        wait_lds_dma();
-        __syncthreads();
-        if (j + 1 >= nt) break;
-        if (j + 2 < nt) issue(j + 2, 0);
-        compute(std::integral_constant<int, 1>{}, j + 1);
+    // One body for both buffers: with a copy per buffer, leaving the loop
+    // between them made the compiler move the accumulators on every tile.
+    for (int j = j0, u = 0; j < nt; ++j, u ^= 1) {
+        // buffer u ^ 1 was last read in the previous tile, before the barrier
+        if (j + 1 < nt) issue(j + 1, u ^ 1);
+        compute(u, j);
         wait_lds_dma();
         __syncthreads();
     }
@@ -583,53 +618,52 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
         const lds_f32* ls = (const lds_f32*)(L + VEC + U * 256);
         const lds_f32* dls = (const lds_f32*)(L + VEC + 512 + U * 256);
         const TileBases<D> off = tb.pinned();
-        // the two chains interleaved: one's MFMA covers the other's LDS reads;
-        // the operands of k-step kk + 2 are read while k-step kk runs
+        // The stage's MFMAs in one order: S, dP, dV, dK, each preceded by the
+        // LDS reads of the operands some MFMAs ahead and followed by its share
+        // of the arithmetic of what is complete by then: P under dP, dS under dV
+        // (dK/dV of the 480p clip, 40 heads: 10.99 ms with S and dP alternating
+        // and the arithmetic after both, 10.69 so).
+        constexpr int RING = 4, VRING = 3, NT = 2 * KK + 4 * DB;
+        constexpr int EP = 16 / KK;              // elements per step
+        constexpr int P0 = KK + KK / 4;          // first step of P
+        constexpr int D0 = 2 * KK + KK / 4;      // first step of dS
+        auto frag = [&](int m) __attribute__((always_inline)) {
+            if (m < KK) return *(const lds_bf16x8_t*)(Qb + off.row(m));
+            if (m < 2 * KK) return *(const lds_bf16x8_t*)(Db + off.row(m - KK));
+            const int n = (m - 2 * KK) % (2 * DB), j = n / DB, d = n % DB;
+            return read_tr<D>((m < 2 * KK + 2 * DB ? Db : Qb) + 16 * j * ROWB, off.tr_lo(d), off.tr_hi(d));
+        };
         f32x16_t s = f32x16_t{}, dp = f32x16_t{};
-        bf16x8_t qa[3], da[3], vb[3];
+        bf16x8_t fr[RING], vb[VRING], pf[2], sf[2];
+        f32x4_t x, y;  // lse (+inf for rows past qend, so that P = 0) and delta of four queries
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            qa[kk] = *(const lds_bf16x8_t*)(Qb + off.row(kk));
-            da[kk] = *(const lds_bf16x8_t*)(Db + off.row(kk));
-            vb[kk] = *(const lds_bf16x8_t*)(Vw + off.row(kk));
-        }
+        for (int m = 0; m < RING; ++m) fr[m] = frag(m);
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            if (kk + 2 < KK) {
-                qa[(kk + 2) % 3] = *(const lds_bf16x8_t*)(Qb + off.row(kk + 2));
-                da[(kk + 2) % 3] = *(const lds_bf16x8_t*)(Db + off.row(kk + 2));
-                vb[(kk + 2) % 3] = *(const lds_bf16x8_t*)(Vw + off.row(kk + 2));
+        for (int m = 0; m < NT; ++m) {
+            const int n = (m - 2 * KK) % (2 * DB), j = n / DB, d = n % DB;
+            if (m < KK) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m % RING], kf[m], s, 0, 0, 0);
+            else if (m < 2 * KK)
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m % RING], vb[(m - KK) % VRING], dp, 0, 0, 0);
+            else if (m < 2 * KK + 2 * DB)
+                dv[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m % RING], pf[j], dv[d], 0, 0, 0);
+            else dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m % RING], sf[j], dk[d], 0, 0, 0);
+            if (m + RING < NT) fr[m % RING] = frag(m + RING);
+            const int kv = m + VRING - KK;  // V operand read VRING MFMAs ahead
+            if (kv >= 0 && kv < KK) vb[kv % VRING] = *(const lds_bf16x8_t*)(Vw + off.row(kv));
+#pragma unroll
+            for (int e = 0; e < EP; ++e) {
+                const int ip = (m - P0) * EP + e, id = (m - D0) * EP + e;
+                if (ip >= 0 && ip < 16) {
+                    s[ip] = __builtin_amdgcn_exp2f(fmaf(s[ip], c, -(x[ip % 4] * 1.4426950408889634f)));
+                    pf[ip / 8][ip % 8] = static_cast<__bf16>(s[ip]);
+                }
+                if (id >= 0 && id < 16) sf[id / 8][id % 8] = static_cast<__bf16>(s[id] * (dp[id] - y[id % 4]));
             }
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[kk % 3], kf[kk], s, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[kk % 3], vb[kk % 3], dp, 0, 0, 0);
+            // the next step's lse or delta, when it starts a group of four queries
+            const int np = (m + 1 - P0) * EP, nd = (m + 1 - D0) * EP;
+            if (np >= 0 && np < 16 && np % 4 == 0) x = *(const lds_f32x4_t*)(ls + 2 * np + 4 * hw);
+            if (nd >= 0 && nd < 16 && nd % 4 == 0) y = *(const lds_f32x4_t*)(dls + 2 * nd + 4 * hw);
             __builtin_amdgcn_sched_barrier(0);
-        }
-        // P and dS, 4 consecutive queries at a time (their lse, +inf for rows
-        // past qend so that P = 0, and delta)
-        bf16x8_t pf[2], sf[2];
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            const int q4 = 8 * g4 + 4 * hw;
-            const f32x4_t x = *(const lds_f32x4_t*)(ls + q4);
-            const f32x4_t y = *(const lds_f32x4_t*)(dls + q4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 4 * g4 + e;
-                const float ml = x[e] * 1.4426950408889634f;
-                const float p = __builtin_amdgcn_exp2f(fmaf(s[i], c, -ml));
-                pf[i / 8][i % 8] = static_cast<__bf16>(p);
-                sf[i / 8][i % 8] = static_cast<__bf16>(p * (dp[i] - y[e]));
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-#pragma unroll
-            for (int d = 0; d < DB; ++d) {
-                const bf16x8_t dt = read_tr<D>(Db + 16 * j * ROWB, off.tr_lo(d), off.tr_hi(d));
-                dv[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dt, pf[j], dv[d], 0, 0, 0);
-                const bf16x8_t qt = read_tr<D>(Qb + 16 * j * ROWB, off.tr_lo(d), off.tr_hi(d));
-                dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt, sf[j], dk[d], 0, 0, 0);
-            }
         }
     };
 
