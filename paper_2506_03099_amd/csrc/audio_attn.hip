@@ -14,9 +14,10 @@
 //
 // Two kinds of workgroup share one launch:
 //   - compute workgroups, one per (batch, head, latent frame, part of the
-//     frame's 32-row blocks; a part takes every parts-th block), 8 waves:
-//     waves 4-7 read the part's face ids into registers; then waves 0-3 issue
-//     the direct global->LDS loads of stream 0's audio window (K and V rows,
+//     frame's 32-row blocks; a part takes every parts-th block) and, where
+//     that still leaves CUs free, per stream (else the streams are taken in
+//     turn), 8 waves: waves 4-7 read the part's face ids into registers; then
+//     waves 0-3 issue the direct global->LDS loads of the first stream's audio window (K and V rows,
 //     16-byte chunks swizzled per row), before the face ids are known. Per
 //     stream used by the part's rows, waves 4-7 compact the rows of that
 //     stream into a list in row order (ballots, per-wave counts in LDS, one
@@ -156,8 +157,15 @@ __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const Au
     const int fw = wave - (kAudioWaves - NFW);  // face wave index (valid for face waves)
 
     const int id = xcd_logical_id(blockIdx.x, a.n_cwg);
-    const int part = id % a.parts;
-    int rest = id / a.parts;
+    // one stream per workgroup, or (one_stream == 0) all of them in turn
+    int rest = id;
+    int m0 = 0;
+    if (a.one_stream) {
+        m0 = rest % a.M;
+        rest /= a.M;
+    }
+    const int part = rest % a.parts;
+    rest /= a.parts;
     const int fi = rest % a.n_frames;
     rest /= a.n_frames;
     const int h = rest % a.H;
@@ -234,9 +242,9 @@ __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const Au
         }
     }
     lds_barrier();  // the face-id loads go out first
-    // stream 0's window is the first one needed unless stream 0 is not used:
-    // its loads go out before the face ids are known
-    if (dma_wave) stage_dma(0);
+    // stream m0's window is the first one needed unless that stream is not
+    // used: its loads go out before the face ids are known
+    if (dma_wave) stage_dma(m0);
     uint32_t used = 0;
     if (face_wave) {
         const int ft = tid - (kAudioThreads - FT);
@@ -259,6 +267,7 @@ __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const Au
     uint32_t streams = 0;
 #pragma unroll
     for (int w = 0; w < kAudioWaves; ++w) streams |= used_l[w];
+    if (a.one_stream) streams &= 1u << m0;
 
     const float c = a.scale_log2;
     // Per-lane LDS byte offsets of the operand fragments of a 32-key tile
@@ -503,7 +512,7 @@ __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const Au
         const int m = __builtin_ctz(streams);
         streams &= streams - 1;
         if (!first) lds_barrier();  // every wave is done with the previous window and list
-        if (dma_wave && (!first || m != 0)) {
+        if (dma_wave && (!first || m != m0)) {
             wait_lds_dma();  // an earlier window load must not land after this one
             stage_dma(m);
         }
@@ -593,7 +602,7 @@ hipError_t launch(const AudioArgs& a, unsigned grid, size_t lds, hipStream_t s) 
 
 hipError_t launch_audio_attn_bf16(const AudioArgs& args, int head_dim, hipStream_t s) {
     AudioArgs a = args;
-    const int64_t n_cwg = static_cast<int64_t>(a.B) * a.H * a.n_frames * a.parts;
+    int64_t n_cwg = static_cast<int64_t>(a.B) * a.H * a.n_frames * a.parts;
     if (n_cwg < 1 || n_cwg > INT32_MAX / 2) return hipErrorInvalidValue;
     // Zero-fill workgroups: the CUs the compute workgroups leave free (a
     // quarter of the chip at least), with at least 16 token rows each.
@@ -609,6 +618,12 @@ hipError_t launch_audio_attn_bf16(const AudioArgs& args, int head_dim, hipStream
         if (cus < 1) return hipErrorInvalidValue;
         cu_count[dev].store(cus, std::memory_order_relaxed);
     }
+    // With several streams, a workgroup per stream as long as these leave the
+    // zero-fill workgroups their quarter of the chip: two faces, 480p chunk, 8
+    // heads (48 workgroups) 18.4 -> 11.0 us, three faces, 24 heads (144) 21.3 ->
+    // 9.6; at 40 heads and two faces (240) the zeros wait and 18.8 becomes 22.8.
+    a.one_stream = a.M > 1 && n_cwg * a.M <= cus - cus / 4;
+    if (a.one_stream) n_cwg *= a.M;
     const int64_t rows = static_cast<int64_t>(a.B) * a.n;
     int64_t nz = n_cwg < cus ? std::max<int64_t>(cus - n_cwg, cus / 4) : cus / 4;
     nz = std::max<int64_t>(1, std::min(nz, (rows + 15) / 16));
