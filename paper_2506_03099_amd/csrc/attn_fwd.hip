@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
         const float p1 = __builtin_amdgcn_exp2f(x[(e + 1) >> 4][(e + 1) & 15]);
         pf[e >> 3][e & 7] = static_cast<__bf16>(p0);
         pf[e >> 3][(e & 7) + 1] = static_cast<__bf16>(p1);
-        lt += p0 + p1;
+        lt = e < 4 ? p0 + p1 : lt + (p0 + p1);
     };
 
     // ---- prologue: tiles 0..3 of K and 0..1 of V in flight, S(0) and its
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
         const uint32_t kb1 = kbuf(u + 1), kb2 = kbuf(u + 2), vb0 = vbuf(u);
         refresh(t);
         bf16x8_t pf[4];
-        float lt0 = 0.f, lt1 = 0.f;
+        float lt0, lt1;
         nx[0] = nx[1] = f32x16_t{};
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -571,7 +571,6 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
             l_run *= alpha;
 #pragma unroll
             for (int d = 0; d < DB; ++d) acc[d] *= alpha;
-            lt0 = lt1 = 0.f;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
