@@ -254,16 +254,19 @@ def tm_qkv_produce(cache: KVCache, chunk: int, q, k, v, q_gain=None, k_gain=None
     return q_out
 
 
-def _workspace(nbytes: int, device, stream: int):
+def _workspace(nbytes: int, q, stream: int):
     """A workspace for one call on `stream`: memory of torch's allocator, which
     hands it out again in the order of the current stream once the call has
     returned. None (the call then runs without) where that order does not cover
-    the call: another stream than the current one, or a stream under capture;
-    and where the memory is not to be had."""
-    if nbytes == 0 or stream != _current_stream() or torch.cuda.is_current_stream_capturing():
+    the call: q a plain address or on another device than the current one,
+    another stream than the current one, or a stream under capture; and where
+    the memory is not to be had."""
+    if (nbytes == 0 or not isinstance(q, torch.Tensor)
+            or q.get_device() != torch._C._cuda_getDevice()
+            or stream != _current_stream() or torch.cuda.is_current_stream_capturing()):
         return None
     try:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        return torch.empty(nbytes, dtype=torch.uint8, device=q.device)
     except torch.cuda.OutOfMemoryError:
         return None
 
@@ -277,7 +280,7 @@ def _fwd(desc, q, q_chunk, cache, k, v, n_frames, o, o_f32, lse, stream):
     if desc.dtype == TM_BF16:
         n = L.tm_sparse_causal_attn_fwd_workspace(d, q_chunk, h, n_frames)
         if n:
-            ws = _workspace(n, q.device, stream)
+            ws = _workspace(n, q, stream)
     _check(L.tm_sparse_causal_attn_fwd_ws(d, _ptr(q), q_chunk, h, _ptr(k), _ptr(v), n_frames, _ptr(o),
                                           o_f32, _ptr(lse), _ptr(ws), n, stream))
     return o
@@ -352,7 +355,7 @@ def tm_sparse_causal_attn_bwd(desc: tm_attn_desc, n_frames: int, q, k, v, o, lse
     d = ctypes.byref(desc)
     stream = _stream(stream)
     n = lib().tm_sparse_causal_attn_bwd_workspace(d, n_frames)
-    ws = _workspace(n, q.device, stream)
+    ws = _workspace(n, q, stream)
     _check(lib().tm_sparse_causal_attn_bwd_ws(d, n_frames, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
                                               _ptr(dout), _ptr(delta), _ptr(dq), _ptr(dk), _ptr(dv),
                                               _ptr(ws), n, stream))

@@ -81,3 +81,24 @@ def test_split_backward_matches_oracle(tm, B, H, D, T, C, R, W, frames, splits):
             assert worst <= 1.0, f"{route} {name}: error {worst:.3f} x the bound"
     for a, b in zip(got["workspace"], again):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+def test_split_backward_with_plain_addresses(tm):
+    # q given as an address, the outputs as tensors: the call without a workspace
+    desc = tm.make_desc(1, 1, 128, 100, 3, 1, 1, "bf16")
+    rng = np.random.default_rng(5)
+    q, k, v, do = (_bf16(rng, (1, 1100, 1, 128), i < 2)[1] for i in range(4))
+    d = ctypes.byref(desc)
+    assert tm.lib().tm_sparse_causal_attn_bwd_workspace(d, 11) > 0
+    lse = torch.empty(1, 1, 1100, dtype=torch.float32, device="cuda")
+    o = tm.tm_sparse_causal_attn_fwd(desc, q, -1, k=k, v=v, n_frames=11, lse=lse)
+    p = tm._ptr
+    delta = torch.empty_like(lse)
+    want, got = ([torch.full_like(q, float("nan")) for _ in range(3)] for _ in range(2))
+    st = tm.lib().tm_sparse_causal_attn_bwd(d, 11, p(q), p(k), p(v), p(o), p(lse), p(do), p(delta),
+                                            *map(p, want), tm._stream(None))
+    assert st == tm.TM_OK, tm.tm_last_error()
+    tm.tm_sparse_causal_attn_bwd(desc, 11, p(q), k, v, o, lse, do, None, *got)
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))

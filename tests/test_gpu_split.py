@@ -171,6 +171,20 @@ def test_split_off_the_current_stream_and_under_capture(tm):
         assert torch.equal(o.view(torch.int16), want.view(torch.int16))
 
 
+def test_split_with_plain_addresses(tm):
+    # tensors given as addresses: the call without a workspace
+    desc = tm.make_desc(1, 2, 128, 256, 3, 1, 1, "bf16")
+    d = draw_qkv_sequence(Workload(840, "split", "bf16", 1, 2, 128, 256, 3, 1, 1, n_frames=8))
+    q, k, v = (to_dev(d[n], d[n + "_bits"], "bf16") for n in "qkv")
+    assert _bytes(tm, desc, -1, None, 8) > 0
+    want = _plain(tm, desc, q, -1, k=k, v=v, n_frames=8)
+    o = torch.empty_like(q)
+    tm.tm_sparse_causal_attn_fwd(desc, q.data_ptr(), -1, k=k.data_ptr(), v=v.data_ptr(), n_frames=8,
+                                 o=o.data_ptr())
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), want.view(torch.int16))
+
+
 def test_split_workspace_is_checked(tm):
     desc = tm.make_desc(1, 2, 128, 256, 3, 1, 1, "bf16")
     q, k, v = (torch.zeros((1, 2048, 2, 128), dtype=torch.bfloat16, device="cuda") for _ in range(3))
