@@ -130,7 +130,8 @@ __device__ __forceinline__ void zero_fill_rows(const AudioArgs& a, int z, lds_u8
     }
 }
 
-template <int D, bool OF32, bool QS>
+// ONE: a workgroup takes one stream's rows, not each stream's in turn.
+template <int D, bool OF32, bool QS, bool ONE>
 __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const AudioArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     if (static_cast<int>(blockIdx.x) >= a.n_cwg) {  // uniform over the workgroup
@@ -157,10 +158,9 @@ __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const Au
     const int fw = wave - (kAudioWaves - NFW);  // face wave index (valid for face waves)
 
     const int id = xcd_logical_id(blockIdx.x, a.n_cwg);
-    // one stream per workgroup, or (one_stream == 0) all of them in turn
     int rest = id;
     int m0 = 0;
-    if (a.one_stream) {
+    if constexpr (ONE) {
         m0 = rest % a.M;
         rest /= a.M;
     }
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const Au
     uint32_t streams = 0;
 #pragma unroll
     for (int w = 0; w < kAudioWaves; ++w) streams |= used_l[w];
-    if (a.one_stream) streams &= 1u << m0;
+    if constexpr (ONE) streams &= 1u << m0;
 
     const float c = a.scale_log2;
     // Per-lane LDS byte offsets of the operand fragments of a 32-key tile
@@ -581,21 +581,26 @@ __global__ __launch_bounds__(kAudioThreads) void audio_attn_bf16_kernel(const Au
 // size, which covers every launch); concurrent first calls set the same value.
 constexpr int kMaxDevices = 64;
 
-template <int D, bool OF32, bool QS>
-hipError_t launch(const AudioArgs& a, unsigned grid, size_t lds, hipStream_t s) {
+template <int D, bool OF32, bool QS, bool ONE>
+hipError_t launch_one(const AudioArgs& a, unsigned grid, size_t lds, hipStream_t s) {
     static std::atomic<bool> attr_set[kMaxDevices];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     if (!attr_set[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&audio_attn_bf16_kernel<D, OF32, QS>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&audio_attn_bf16_kernel<D, OF32, QS, ONE>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kAudioMaxLds));
         if (e != hipSuccess) return e;
         attr_set[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((audio_attn_bf16_kernel<D, OF32, QS>), dim3(grid), dim3(kAudioThreads), lds, s, a);
+    hipLaunchKernelGGL((audio_attn_bf16_kernel<D, OF32, QS, ONE>), dim3(grid), dim3(kAudioThreads), lds, s, a);
     return hipGetLastError();
+}
+
+template <int D, bool OF32, bool QS>
+hipError_t launch(const AudioArgs& a, unsigned grid, size_t lds, bool one_stream, hipStream_t s) {
+    return one_stream ? launch_one<D, OF32, QS, true>(a, grid, lds, s) : launch_one<D, OF32, QS, false>(a, grid, lds, s);
 }
 
 }  // namespace
@@ -622,8 +627,10 @@ hipError_t launch_audio_attn_bf16(const AudioArgs& args, int head_dim, hipStream
     // zero-fill workgroups their quarter of the chip: two faces, 480p chunk, 8
     // heads (48 workgroups) 18.4 -> 11.0 us, three faces, 24 heads (144) 21.3 ->
     // 9.6; at 40 heads and two faces (240) the zeros wait and 18.8 becomes 22.8.
-    a.one_stream = a.M > 1 && n_cwg * a.M <= cus - cus / 4;
-    if (a.one_stream) n_cwg *= a.M;
+    // A kernel of its own: as an argument the choice cost the one-face call 0.08
+    // of its 12 us.
+    const bool one_stream = a.M > 1 && n_cwg * a.M <= cus - cus / 4;
+    if (one_stream) n_cwg *= a.M;
     const int64_t rows = static_cast<int64_t>(a.B) * a.n;
     int64_t nz = n_cwg < cus ? std::max<int64_t>(cus - n_cwg, cus / 4) : cus / 4;
     nz = std::max<int64_t>(1, std::min(nz, (rows + 15) / 16));
@@ -643,11 +650,11 @@ hipError_t launch_audio_attn_bf16(const AudioArgs& args, int head_dim, hipStream
     if (a.q_stage) lds = staged;
     const unsigned g = static_cast<unsigned>(n_cwg + nz);
     if (a.q_stage) {
-        if (head_dim == 128) return a.o_f32 ? launch<128, true, true>(a, g, lds, s) : launch<128, false, true>(a, g, lds, s);
-        if (head_dim == 64) return a.o_f32 ? launch<64, true, true>(a, g, lds, s) : launch<64, false, true>(a, g, lds, s);
+        if (head_dim == 128) return a.o_f32 ? launch<128, true, true>(a, g, lds, one_stream, s) : launch<128, false, true>(a, g, lds, one_stream, s);
+        if (head_dim == 64) return a.o_f32 ? launch<64, true, true>(a, g, lds, one_stream, s) : launch<64, false, true>(a, g, lds, one_stream, s);
     } else {
-        if (head_dim == 128) return a.o_f32 ? launch<128, true, false>(a, g, lds, s) : launch<128, false, false>(a, g, lds, s);
-        if (head_dim == 64) return a.o_f32 ? launch<64, true, false>(a, g, lds, s) : launch<64, false, false>(a, g, lds, s);
+        if (head_dim == 128) return a.o_f32 ? launch<128, true, false>(a, g, lds, one_stream, s) : launch<128, false, false>(a, g, lds, one_stream, s);
+        if (head_dim == 64) return a.o_f32 ? launch<64, true, false>(a, g, lds, one_stream, s) : launch<64, false, false>(a, g, lds, one_stream, s);
     }
     return hipErrorInvalidValue;
 }

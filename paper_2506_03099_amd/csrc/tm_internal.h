@@ -125,9 +125,8 @@ struct AudioArgs {
     int32_t max_keys_pad;  // most window keys of any frame, rounded up to 32
     int32_t o_f32;         // store o as fp32 (the values before the final rounding)
     float scale_log2;      // softmax scale * log2(e)
-    int32_t one_stream;    // a workgroup takes one stream's rows, not each in turn; set by the launcher
-    int32_t n_cwg;         // compute workgroups (B * H * n_frames * parts, times M with one_stream);
-                           // set by the launcher
+    int32_t n_cwg;         // compute workgroups (B * H * n_frames * parts, times M where each takes
+                           // one stream); set by the launcher
     int32_t zrows;         // token rows per zero-fill workgroup; set by the launcher
     int32_t q_stage;       // queries (and bf16 output rows) staged in LDS; set by the launcher
 };
