@@ -453,7 +453,16 @@ tm_status plan_tiles(const Geo& g, const Plan& p, tmk::AttnArgs* out) {
         int groups = 1;
         while (groups < 4 && waves * groups < 2 * tmk::kF32FillWaves && int64_t(groups) * 64 <= most_keys)
             groups *= 2;
-        if (g.D == 64 && groups == 4 && waves * 8 <= tmk::kF32FillWaves && 8 * 32 <= most_keys) groups = 8;
+        // 8 groups share a SIMD two by two, so they take 2 ceil(blocks / 8) block
+        // times for 4 groups' ceil(blocks / 4), and save 8% where these are
+        // equal: a chunk's call keeps 4 where 8 round up to more than that (two
+        // heads, append and attention: 10 blocks 15.2 us with 4, 19.3 with 8;
+        // 35 blocks 31.0 and 34.8).
+        int64_t blocks = 0;
+        for (const auto& rg : p.ranges) blocks += ceil_div(rg.second - rg.first, 32);
+        const bool uneven = p.mode == 0 && 2 * ceil_div(blocks, 8) * 12 > ceil_div(blocks, 4) * 13;
+        if (g.D == 64 && groups == 4 && waves * 8 <= tmk::kF32FillWaves && 8 * 32 <= most_keys && !uneven)
+            groups = 8;
         a.key_groups = groups;
         BM = tmk::f32_tile_rows(groups);
     }
