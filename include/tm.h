@@ -193,11 +193,12 @@ tm_status tm_sparse_causal_attn_fwd_f32out(const tm_attn_desc* desc, const void*
 
 /* The same two calls (o_f32 = 0 or 1: o as in the first or the second) with a
  * caller-owned workspace for the call's duration on `stream`. Query tiles that
- * do not fill the GPU then share their keys out over several workgroups, whose
- * partial results (fp32 O, running max and row sum) go through the workspace
- * and are merged in a fixed order. Which calls do so, and how, follows from the
- * arguments' sizes alone; the sum over the keys is then ordered differently
- * from the calls without a workspace, the result still deterministic.
+ * do not fill the GPU share their keys out in parts, each with a running max of
+ * its own, whose results (fp32 O, max and row sum) are merged in a fixed order.
+ * Which calls do so, and how, follows from the arguments' sizes alone. With a
+ * workspace the parts run on several workgroups and their results go through
+ * it; without, they run one after the other. The result is the same, bit for
+ * bit.
  * workspace: device memory, 16-byte aligned, not overlapping any other tensor,
  * or NULL. With fewer than tm_sparse_causal_attn_fwd_workspace() bytes (0: the
  * call needs none; also on invalid arguments) it is not used. */

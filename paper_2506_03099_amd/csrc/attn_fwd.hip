@@ -32,6 +32,11 @@
 // tensor, filled by direct global->LDS loads two (V) and four (K) tiles ahead,
 // with one barrier per tile.
 //
+// Query tiles that do not fill the GPU share their keys out in parts, each with
+// a running max of its own: over several workgroups, merged by a second kernel,
+// where the call has a workspace; else in turn in one workgroup, which merges
+// them itself. The arithmetic is the same, and so are the bits.
+//
 // fp32 kernel: fp32 MFMAs (v_mfma_f32_32x32x2_f32) with an exact running max,
 // operands loaded from global memory by the lanes that feed them; the keys of a
 // query tile may be shared out over a workgroup's waves.
@@ -50,10 +55,12 @@ typedef __attribute__((address_space(3))) bf16x4_t lds_bf16x4_t;
 typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
 typedef __attribute__((address_space(3))) f32x4_t lds_f32x4_t;
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
+typedef __attribute__((address_space(5))) f32x4_t lane_f32x4_t;  // private memory of a lane
 
 // Threads per workgroup of the bf16 kernel: 8 waves (two per SIMD) sharing
 // every K/V tile staged in LDS.
 constexpr int kBf16Threads = 512;
+constexpr int kMaxLds = 160 * 1024;  // of a workgroup
 // Wait until at most N LDS operations (and scalar loads) of this wave are
 // outstanding; vector-memory and export counts are left unconstrained.
 template <int N>
@@ -150,6 +157,12 @@ __device__ __forceinline__ TileRanges plan_tile(const AttnArgs& a, int tile, int
     return t;
 }
 
+// 64-key tiles of a query tile's ranges.
+__device__ __forceinline__ int key_tiles(const AttnArgs& a, const TileRanges& t) {
+    if (a.mode == 0) return a.n_ktiles;
+    return (t.e0 - t.b0 + kKeyTile - 1) / kKeyTile + (t.n > 1 ? (t.e1 - t.b1 + kKeyTile - 1) / kKeyTile : 0);
+}
+
 // Range r of a tile. A cache call (CACHE) may have up to kMaxRanges, in the
 // kernel arguments; a whole sequence has at most two, held in registers.
 template <bool CACHE>
@@ -186,7 +199,31 @@ __device__ __forceinline__ int vt_swizzle(int d) { return (d >> 1) & 7; }
 
 
 
-template <int D, bool VT, bool OF32>
+// The merge of a row's parts, added in order: the running max m (log2 domain)
+// and row sum l of the parts so far, and the factors of their O and of the next
+// part's. A part whose row sum is zero (only scores of -inf) adds nothing. Every
+// rounding is spelled out: both places that merge give the same bits.
+struct RowMerge {
+    float m = kNegInf, l = 0.f;
+    float keep = 0.f, take = 0.f;
+    __device__ __forceinline__ void next(float mi, float li) {
+        const float mx = li != 0.f ? fmaxf(m, mi) : m;
+        keep = l != 0.f ? __builtin_amdgcn_exp2f(m - mx) : 0.f;
+        take = li != 0.f ? __builtin_amdgcn_exp2f(mi - mx) : 0.f;
+        l = fmaf(take, li, __fmul_rn(l, keep));
+        m = mx;
+    }
+    __device__ __forceinline__ float fold(float o, float oi) const { return fmaf(take, oi, __fmul_rn(o, keep)); }
+};
+
+// A workgroup takes a query tile or a part of a split one. TURN > 0 (a call
+// without a workspace): TURN workgroups take a split tile, a share of its rows
+// and all of its parts in turn each. With one busy wave on a SIMD a key tile
+// takes 0.75 us there and not 1.1, and a part's end about 0.3, in a branch of the
+// one continuous walk (a walk of its own per part took 5 us for each: the tiles
+// in flight drain and the compiler spills): 480p chunk with 1, 3, 5 heads: 143,
+// 144, 148 us (44, 85, 130 with a workspace; 187, 190, 191 unsplit).
+template <int D, bool VT, bool OF32, int TURN>
 __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const AttnArgs a) {
     constexpr int BM = kTileRowsBf16;  // query rows per workgroup
     constexpr int BN = kKeyTile;       // keys per tile
@@ -210,7 +247,9 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
 
     // K tile j sits in buffer j % 4 of the first four, V tile j in buffer
     // j % 4 of the last four.
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NBUF * TILEB];
+    constexpr int SUMB = TURN > 0 ? NW / TURN * 32 * D * 4 : 0;  // O of the parts before, if there is room
+    constexpr bool LSUM = SUMB > 0 && 2 * NBUF * TILEB + SUMB <= kMaxLds;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NBUF * TILEB + (LSUM ? SUMB : 0)];
     lds_u8* const L = (lds_u8*)(smem);
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(L));
 
@@ -228,15 +267,24 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     if (!split) {
         id = xcd_logical_id(blockIdx.x, a.n_whole);
     } else {
-        const int sid = xcd_logical_id(blockIdx.x - a.n_whole, (total - a.n_whole) * a.parts);
-        id = a.n_whole + sid / a.parts;
-        part = sid % a.parts;
+        const int each = TURN > 0 ? TURN : a.parts;  // workgroups per split tile
+        const int sid = xcd_logical_id(blockIdx.x - a.n_whole, (total - a.n_whole) * each);
+        id = a.n_whole + sid / each;
+        part = sid % each;
     }
     const int tile = id % a.n_qtiles;
     const int bh = id / a.n_qtiles;
     const int head = bh % a.H;
     const int bat = bh / a.H;
-    const TileRanges tr = plan_tile(a, tile, BM);
+    TileRanges tr = plan_tile(a, tile, BM);
+    if constexpr (TURN > 0) {
+        if (split) {
+            tr.q0 += part * (BM / TURN);
+            tr.q1 = min(tr.q1, tr.q0 + BM / TURN);
+            if (tr.q0 >= tr.q1) return;
+            part = 0;
+        }
+    }
 
     const __bf16* qp = static_cast<const __bf16*>(a.q) + bat * a.q_sb + head * a.q_sh;
     const __bf16* kp = static_cast<const __bf16*>(a.k) + bat * a.k_sb + head * a.k_sh;
@@ -251,12 +299,14 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     struct Walk {
         int kb, ke, r;
     };
-    auto range_tiles = [&](int r) {
-        return (range_end<VT>(a, tr, r) - range_begin<VT>(a, tr, r) + BN - 1) / BN;
-    };
-    int n;
-    if constexpr (VT) n = a.n_ktiles;
-    else n = range_tiles(0) + (tr.n > 1 ? range_tiles(1) : 0);
+    int n = VT ? a.n_ktiles : key_tiles(a, tr);
+    // Parts of the tile (no more than it has key tiles): part i takes tiles
+    // [n i / parts, n (i + 1) / parts).
+    int parts = 1;
+    if (split) {
+        parts = min(a.parts, n);
+        if (part >= parts) return;
+    }
     // one past the walk's last tile in the current range
     auto tiles_end = [](const Walk& w) { return (w.ke - w.kb + BN - 1) / BN; };
     // Tile j (clamped to the walk's last tile).
@@ -418,11 +468,10 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     // exact maximum (the lazy running max starts from it), x(0) = S(0)*c - m.
     uint32_t offk[NI], offv[NI];  // lane offsets of the loads of the current K and V tiles
     Walk ws{range_begin<VT>(a, tr, 0), range_end<VT>(a, tr, 0), 0};  // tile t+1 (scores)
-    if (split) {
-        // A part takes tiles [j0, j1) of the walk, numbered from 0 here. (It
-        // may have none where tiles see fewer key tiles than there are parts:
-        // its row sums then stay zero.) Loads past j1 fetch tiles that exist.
-        const int j0 = n * part / a.parts, j1 = n * (part + 1) / a.parts;
+    if (TURN == 0 && split) {
+        // A part takes tiles [j0, j1) of the walk, numbered from 0 here. Loads
+        // past j1 fetch tiles that exist.
+        const int j0 = n * part / parts, j1 = n * (part + 1) / parts;
         tile_at(ws, j0);
         ws.kb += BN * j0;
         n = j1 - j0;
@@ -540,6 +589,35 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
             wait_lds_reads<0>();
         }
     };
+    // TURN: where the current part ends, and the parts before it: O in LDS, or
+    // where that is full in the lane's private memory (the registers are full too).
+    // The walk goes on over a part's end; only the running max, the sum and O start
+    // anew.
+    int part_end = n / parts;
+    RowMerge sum;
+    lds_u8* const sum_l = L + 2 * NBUF * TILEB + __builtin_amdgcn_readfirstlane(wave) * (32 * D * 4) + lane * 16;
+    lane_f32x4_t* sum_p = nullptr;
+    f32x4_t sum_mem[TURN > 0 && !LSUM ? 4 * DB : 1];
+    if constexpr (TURN > 0 && !LSUM) {
+        sum_p = (lane_f32x4_t*)sum_mem;
+        asm volatile("" : "+s"(sum_p));  // (else the compiler takes registers and spills in the key loop)
+    }
+    auto fold_part = [&]() __attribute__((always_inline)) {
+        sum.next(m_run, l_run + __shfl_xor(l_run, 32));
+        if (part == 0) {
+#pragma unroll
+            for (int i = 0; i < 16 * DB; ++i) acc[i / 16][i % 16] = sum.fold(0.f, acc[i / 16][i % 16]);
+        } else {
+#pragma unroll
+            for (int d = 0; d < DB; ++d) {
+                f32x4_t o[4];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) o[g] = LSUM ? *(const lds_f32x4_t*)(sum_l + (4 * d + g) * 1024) : sum_p[4 * d + g];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[d][i] = sum.fold(o[i / 4][i % 4], acc[d][i]);
+            }
+        }
+    };
     // The barrier orders only this workgroup's LDS use: the compiler may not
     // move LDS accesses across it, and no wait is needed for the fragment
     // reads still in flight (their buffer is not written next).
@@ -580,7 +658,12 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
         }
         l_run += lt0 + lt1;
         if (mask_next) mask_tile(nx, tile_at(ws, t + 1));
-        const float nm = -m_run;
+        float nm = -m_run;
+        const bool turn = TURN > 0 && t + 1 == part_end && t + 1 < n;
+        if (turn) {  // tile t+1 starts a part: its exact maximum, as in the prologue
+            const float mx = row_max(nx);
+            nm = mx == kNegInf ? 0.f : -(mx * c);
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
@@ -593,6 +676,23 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
                 dma_pair(i, kptr, offk[i], kbuf(u), vptr, offv[i], NBUF * TILEB + vbuf(u + 2));
             }
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (TURN > 0) if (turn) {
+            fold_part();
+#pragma unroll
+            for (int d = 0; d < DB; ++d) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4_t w{acc[d][4 * g], acc[d][4 * g + 1], acc[d][4 * g + 2], acc[d][4 * g + 3]};
+                    if constexpr (LSUM) *(lds_f32x4_t*)(sum_l + (4 * d + g) * 1024) = w;
+                    else sum_p[4 * d + g] = w;
+                }
+                acc[d] = f32x16_t{};
+            }
+            m_run = -nm;
+            l_run = 0.f;
+            ++part;
+            part_end = n * (part + 1) / parts;
         }
         end_tile();
     };
@@ -627,8 +727,14 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     // store instruction would touch 32 rows for 16 or 32 bytes each (with the
     // queries behind the direct loads above, 3 us less per workgroup: one
     // 256-row tile over 20 key tiles 38.5 -> 35.7 us).
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (split) {
+    float l_tot = l_run + __shfl_xor(l_run, 32);
+    if constexpr (TURN > 0) {
+        if (split) {
+            fold_part();
+            m_run = sum.m;
+            l_tot = sum.l;
+        }
+    } else if (split) {
         // unnormalised, in registers' order: every store is a whole KB
         if (busy) {
             const int64_t at = (static_cast<int64_t>(id - a.n_whole) * a.parts + part) * NW + wave;
@@ -691,8 +797,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
 }
 
 // Merges the parts of the split query tiles: one wave per 32 query rows and 32
-// output dimensions. Parts are added in order (deterministic); a part whose row
-// sum is zero (no keys, or only scores of -inf) adds nothing.
+// output dimensions.
 template <int D, bool OF32>
 __global__ __launch_bounds__(64) void attn_merge_kernel(const AttnArgs a) {
     constexpr int BM = kTileRowsBf16, NW = BM / 32, DB = D / 32;
@@ -710,44 +815,43 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const AttnArgs a) {
 
     const float* p0 = a.part + (static_cast<int64_t>(st) * a.parts * NW + wave) * part_floats(D);
     constexpr int64_t step = NW * part_floats(D);  // from part to part
-    // four parts' loads in flight together (the kernel is bound by their latency)
-    constexpr int U = 4;
+    // Four parts' loads in flight together, and the next four while these are
+    // merged (the kernel is bound by their latency).
+    constexpr int U = 4, G = kMaxParts / U;
+    const int parts = min(a.parts, key_tiles(a, tr));
+    float mi[2][U], li[2][U];
+    f32x4_t ai[2][U][4];
+    auto load = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float* p = p0 + min(U * i + u, parts - 1) * step;
+            mi[i & 1][u] = p[32 * D + lane];
+            li[i & 1][u] = p[32 * D + 64 + lane];
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                ai[i & 1][u][g] = *reinterpret_cast<const f32x4_t*>(p + (4 * d + g) * 256 + 4 * lane);
+        }
+    };
+    RowMerge sum;
     f32x4_t acc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) acc[g] = f32x4_t{};
-    float m = kNegInf, l = 0.f;
-    for (int i = 0; i < a.parts; i += U) {
-        float mi[U], li[U];
-        f32x4_t ai[U][4];
+    load(0);
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        if (i + 1 < G && U * (i + 1) < parts) load(i + 1);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float* p = p0 + min(i + u, a.parts - 1) * step;
-            mi[u] = p[32 * D + lane];
-            li[u] = p[32 * D + 64 + lane];
+            if (U * i + u < parts) {
+                sum.next(mi[i & 1][u], li[i & 1][u]);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) ai[u][g] = *reinterpret_cast<const f32x4_t*>(p + (4 * d + g) * 256 + 4 * lane);
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[g][e] = sum.fold(acc[g][e], ai[i & 1][u][g][e]);
+            }
         }
-        float mx = m;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (i + u >= a.parts) li[u] = 0.f;
-            if (li[u] != 0.f) mx = fmaxf(mx, mi[u]);
-        }
-        const float f0 = l != 0.f ? __builtin_amdgcn_exp2f(m - mx) : 0.f;
-        l *= f0;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) acc[g] *= f0;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float f = li[u] != 0.f ? __builtin_amdgcn_exp2f(mi[u] - mx) : 0.f;
-            l += f * li[u];
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                if (i + u < a.parts) acc[g] += f * ai[u][g];
-        }
-        m = mx;
     }
-    const float inv = 1.f / l;
+    const float inv = 1.f / sum.l;
     const int qrow = tr.q0 + wave * 32 + l32;
     if (qrow >= tr.q1) return;
     const int64_t orow = bat * a.o_sb + head * a.o_sh + qrow * a.o_st + 32 * d + 4 * hw;
@@ -764,7 +868,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const AttnArgs a) {
         }
     }
     if (a.lse != nullptr && d == 0 && hw == 0)
-        a.lse[(static_cast<int64_t>(bat) * a.H + head) * a.Lq + qrow] = (m + __log2f(l)) * 0.69314718055994530942f;
+        a.lse[(static_cast<int64_t>(bat) * a.H + head) * a.Lq + qrow] = (sum.m + __log2f(sum.l)) * 0.69314718055994530942f;
 }
 
 // ----------------------------------------------------------------------------
@@ -1016,10 +1120,20 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
 template <int D, bool VT, bool OF32>
 void launch_bf16(const AttnArgs& a, hipStream_t s) {
     const int split = a.n_qtiles * a.B * a.H - a.n_whole;
-    const dim3 grid(a.n_whole + split * a.parts);
-    hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, VT, OF32>), grid, dim3(kBf16Threads), 0, s, a);
-    if (split > 0)
-        hipLaunchKernelGGL((attn_merge_kernel<D, OF32>), dim3(split * (kTileRowsBf16 / 32) * (D / 32)), dim3(64), 0, s, a);
+    const dim3 block(kBf16Threads);
+    if (split == 0 || a.part != nullptr) {
+        hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, VT, OF32, 0>), dim3(a.n_whole + split * a.parts), block, 0, s, a);
+        if (split > 0)
+            hipLaunchKernelGGL((attn_merge_kernel<D, OF32>), dim3(split * (kTileRowsBf16 / 32) * (D / 32)), dim3(64), 0, s,
+                               a);
+    } else if (4 * split <= kCUs) {
+        // Four workgroups per split tile as long as all of them run at once: at
+        // D = 128 the merged O fits their LDS, two need the lanes' private memory
+        // (one head: 143 us with four, 186 with two).
+        hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, VT, OF32, 4>), dim3(a.n_whole + 4 * split), block, 0, s, a);
+    } else {
+        hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, VT, OF32, 2>), dim3(a.n_whole + 2 * split), block, 0, s, a);
+    }
 }
 template <int D, bool VT>
 void launch_bf16_out(const AttnArgs& a, hipStream_t s) {

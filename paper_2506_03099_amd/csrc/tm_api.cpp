@@ -497,7 +497,7 @@ tmk::AttnSplit plan_split(const Geo& g, const Plan& p, const tmk::AttnArgs& a) {
     if (rest == 0) return sp;
     const int64_t keys = p.mode == 0 ? a.n_ktiles
                                      : ceil_div(std::min(p.seq_len, g.RT + (g.W + 1) * g.CT), tmk::kKeyTile);
-    const int64_t parts = std::min<int64_t>({tmk::kCUs / rest, keys / 4, 16});
+    const int64_t parts = std::min<int64_t>({tmk::kCUs / rest, keys / 4, tmk::kMaxParts});
     if (parts < 2 || keys - ceil_div(keys, parts) < 10) return sp;
     sp.whole = tiles - rest;
     sp.parts = int(parts);
@@ -573,11 +573,11 @@ tm_status attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
     a.Lq = int32_t(p.Lq);
     a.scale_log2 = float(double(g.scale) * 1.4426950408889634);
     if ((st = plan_tiles(g, p, &a)) != TM_OK) return st;
-    a.n_whole = a.n_qtiles * a.B * a.H;
-    a.parts = 1;
+    const tmk::AttnSplit sp = plan_split(g, p, a);
+    a.n_whole = int32_t(sp.whole);
+    a.parts = sp.parts;
     if (workspace != nullptr) {
         // A workspace that is too small is not used.
-        const tmk::AttnSplit sp = plan_split(g, p, a);
         const size_t need = split_bytes(g, a, sp);
         if (need > 0 && need <= workspace_bytes) {
             if ((st = check_ptr(workspace, need, "workspace")) != TM_OK) return st;
@@ -585,8 +585,6 @@ tm_status attn_fwd(const tm_attn_desc* desc, const void* q, int32_t q_chunk,
                 overlaps(workspace, need, a.k, kv_bytes) || overlaps(workspace, need, a.v, kv_bytes) ||
                 (lse != nullptr && overlaps(workspace, need, lse, lse_bytes)))
                 return fail(TM_E_ARG, "workspace overlaps another tensor");
-            a.n_whole = int32_t(sp.whole);
-            a.parts = sp.parts;
             a.part = static_cast<float*>(workspace);
         }
     }

@@ -23,7 +23,9 @@ __host__ __device__ constexpr int64_t part_floats(int head_dim) { return 32 * in
 // Key split of the query tiles that do not fill a whole round of the chip's
 // CUs: `whole` tiles (a multiple of kCUs) run over all their keys, each of the
 // others is shared out over `parts` workgroups, whose partial results a second
-// kernel merges. parts = 1: no split.
+// kernel merges (without a workspace for these: the parts run one after the
+// other in a workgroup, to the same bits). parts = 1: no split.
+constexpr int kMaxParts = 16;
 struct AttnSplit {
     int64_t whole = 0;
     int parts = 1;
@@ -66,8 +68,8 @@ struct AttnArgs {
     int32_t n_qtiles;  // query tiles per (batch, head)
     int32_t key_groups;  // fp32 kernel: shares of a tile's keys (1, 2, 4 or 8)
     int32_t n_whole;     // bf16 kernel: tiles (of all heads) that are not split
-    int32_t parts;       // bf16 kernel: workgroups per split tile (1: none is split)
-    float* part;         // bf16 kernel: [split tile][part][wave][part_floats]
+    int32_t parts;       // bf16 kernel: key shares of a split tile (1: none is split)
+    float* part;         // bf16 kernel: [split tile][part][wave][part_floats], or null
     // mode 0: every query row of the buffer belongs to one chunk and sees the
     //         same key ranges (streaming form, or one chunk of a sequence);
     // mode 1: the buffer holds a whole sequence (row i = position i); each

@@ -257,10 +257,10 @@ def tm_qkv_produce(cache: KVCache, chunk: int, q, k, v, q_gain=None, k_gain=None
 def _workspace(nbytes: int, q, stream: int):
     """A workspace for one call on `stream`: memory of torch's allocator, which
     hands it out again in the order of the current stream once the call has
-    returned. None (the call then runs without) where that order does not cover
-    the call: q a plain address or on another device than the current one,
-    another stream than the current one, or a stream under capture; and where
-    the memory is not to be had."""
+    returned. None (the call then runs without, to the same bits) where that
+    order does not cover the call: q a plain address or on another device than
+    the current one, another stream than the current one, or a stream under
+    capture; and where the memory is not to be had."""
     if (nbytes == 0 or not isinstance(q, torch.Tensor)
             or q.get_device() != torch._C._cuda_getDevice()
             or stream != _current_stream() or torch.cuda.is_current_stream_capturing()):

@@ -1,7 +1,8 @@
 """GPU parity of the forward's key split (the calls with a workspace).
 
 Query tiles that do not fill the GPU share their keys out over several
-workgroups and a second kernel merges the parts. Each geometry runs with the
+workgroups and a second kernel merges the parts; without a workspace the parts
+run one after the other, to the same bits. Each geometry runs with the
 workspace (the binding's ordinary calls) and without (the C entry points that
 take none). The fp32 output of both is held to the oracle within
 2^-9 * (P |V|) + 1e-4 * RMS per element: every weight is rounded to bf16 for the
@@ -40,6 +41,12 @@ def _plain(tm, desc, q, q_chunk, cache=None, k=None, v=None, n_frames=0, lse=Non
             tm._ptr(v), n_frames, tm._ptr(o), tm._ptr(lse), tm._stream(None))
     assert st == tm.TM_OK, tm.tm_last_error()
     return o
+
+
+def _plain_into(tm, desc, q, q_chunk, o, lse, k=None, v=None, n_frames=0):
+    st = tm.lib().tm_sparse_causal_attn_fwd(ctypes.byref(desc), tm._ptr(q), q_chunk, None, tm._ptr(k), tm._ptr(v),
+                                            n_frames, tm._ptr(o), tm._ptr(lse), tm._stream(None))
+    assert st == tm.TM_OK, tm.tm_last_error()
 
 
 def _bytes(tm, desc, q_chunk, cache=None, n_frames=0):
@@ -169,6 +176,73 @@ def test_split_off_the_current_stream_and_under_capture(tm):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(o.view(torch.int16), want.view(torch.int16))
+
+
+# B, H, D, T, C, R, W, rows of the streamed chunk 3 (0: all)
+ROUTES = [
+    (1, 2, 128, 300, 3, 1, 1, 0),     # 8 split tiles: four workgroups walk each tile's parts
+    (2, 5, 128, 500, 3, 3, 0, 33),    # 33 rows: most of these workgroups have none
+    (1, 3, 64, 301, 2, 2, 2, 250),
+    (1, 20, 128, 300, 3, 1, 1, 777),  # 80 split tiles: two workgroups each, O in private memory
+    (1, 33, 64, 200, 2, 3, 3, 0),     # 66 at D = 64
+    (1, 258, 64, 150, 2, 1, 3, 0),    # 512 whole tiles beside 4 split ones
+]
+
+
+def _same_bits(got, want):
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("B,H,D,T,C,R,W,rows", ROUTES)
+def test_split_bits_do_not_depend_on_the_workspace_streamed(tm, B, H, D, T, C, R, W, rows):
+    say(f"split routes, stream: B={B} H={H} D={D} T={T} C={C} R={R} W={W} rows={rows}")
+    desc = tm.make_desc(B, H, D, T, C, R, W, "bf16")
+    w = Workload(860 + T, "split", "bf16", B, H, D, T, C, R, W)
+    cache = tm.KVCache(desc)
+    for t in range(4):
+        d = draw_chunk(w, t, rows if t == 3 and rows else None)
+        q, k, v = (to_dev(d[n], d[n + "_bits"], "bf16") for n in "qkv")
+        tm.tm_kv_append(cache, t, k, v)
+    assert _bytes(tm, desc, 3, cache) > 0
+    lse = [torch.empty((B, H, q.shape[1]), dtype=torch.float32, device="cuda") for _ in range(2)]
+    want = (tm.tm_sparse_causal_attn_fwd(desc, q, 3, cache=cache, lse=lse[0]), lse[0],
+            tm.tm_sparse_causal_attn_fwd_f32out(desc, q, 3, cache=cache))
+    got = (_plain(tm, desc, q, 3, cache=cache, lse=lse[1]), lse[1], _plain(tm, desc, q, 3, cache=cache, f32=True))
+    torch.cuda.synchronize()
+    _same_bits(got, want)
+
+
+# B, H, D, T, C, R, W, frames
+SEQUENCE_ROUTES = [
+    (1, 2, 128, 256, 3, 1, 1, 8),     # c_0's tiles have fewer key tiles than there are parts
+    (1, 1, 64, 200, 2, 3, 2, 11),
+    (1, 10, 128, 250, 3, 1, 1, 7),    # 70 split tiles
+    (1, 12, 64, 250, 3, 1, 1, 7),     # 84 at D = 64
+]
+
+
+@pytest.mark.parametrize("B,H,D,T,C,R,W,frames", SEQUENCE_ROUTES)
+def test_split_bits_do_not_depend_on_the_workspace_sequence(tm, B, H, D, T, C, R, W, frames):
+    say(f"split routes, sequence: B={B} H={H} D={D} T={T} C={C} R={R} W={W} frames={frames}")
+    desc = tm.make_desc(B, H, D, T, C, R, W, "bf16")
+    d = draw_qkv_sequence(Workload(880 + T, "split", "bf16", B, H, D, T, C, R, W, n_frames=frames))
+    q, k, v = (to_dev(d[n], d[n + "_bits"], "bf16") for n in "qkv")
+    for chunk in (-1, 2):  # the whole sequence, and one chunk's queries
+        if chunk >= 0:
+            start = R * T + (chunk - 1) * C * T
+            q = q[:, start:start + C * T].contiguous()
+        kw = dict(k=k, v=v, n_frames=frames)
+        assert _bytes(tm, desc, chunk, None, frames) > 0
+        lse = [torch.empty((B, H, q.shape[1]), dtype=torch.float32, device="cuda") for _ in range(3)]
+        want = (tm.tm_sparse_causal_attn_fwd(desc, q, chunk, lse=lse[0], **kw), lse[0],
+                tm.tm_sparse_causal_attn_fwd_f32out(desc, q, chunk, **kw))
+        got = (_plain(tm, desc, q, chunk, lse=lse[1], **kw), lse[1], _plain(tm, desc, q, chunk, f32=True, **kw))
+        inplace = q.clone()
+        _plain_into(tm, desc, inplace, chunk, inplace, lse[2], **kw)
+        torch.cuda.synchronize()
+        _same_bits(got, want)
+        _same_bits((inplace, lse[2]), want)
 
 
 def test_split_with_plain_addresses(tm):
