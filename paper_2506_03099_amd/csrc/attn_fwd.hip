@@ -990,7 +990,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
     f32x16_t acc[DB];
 #pragma unroll
     for (int d = 0; d < DB; ++d) acc[d] = f32x16_t{};
-    float m = kNegInf, l = 0.f;  // running max of the row (log2 domain), this lane's part of its sum
+    // Running max of the row (log2 domain), what the exponents subtract (0 while
+    // the row has only seen scores of -inf, which then add nothing), this lane's
+    // part of the row's sum.
+    float m = kNegInf, ms = 0.f, l = 0.f;
     const float c = a.scale_log2;
     if (busy) {
         const float* row = k_base(k0, ke);
@@ -1034,7 +1037,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
             const float m_new = fmaxf(m, fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c);
             if (__any(m_new > m)) {
-                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+                ms = m_new == kNegInf ? 0.f : m_new;
+                const float alpha = __builtin_amdgcn_exp2f(m - ms);
                 l *= alpha;
 #pragma unroll
                 for (int d = 0; d < DB; ++d) acc[d] *= alpha;
@@ -1042,7 +1046,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                s0[i] = __builtin_amdgcn_exp2f(fmaf(s0[i], c, -m));
+                s0[i] = __builtin_amdgcn_exp2f(fmaf(s0[i], c, -ms));
                 l += s0[i];
             }
 #pragma unroll
@@ -1076,7 +1080,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
         if (kg < half) {
             const float m2 = mine[NR][lane];
             const float mm = fmaxf(m, m2);
-            // a group without keys (or whose scores are all -inf) adds nothing
+            // a group without keys, or whose scores are all -inf, has l = 0 and O = 0
             const float f1 = m == kNegInf ? 0.f : exp2f(m - mm), f2 = m2 == kNegInf ? 0.f : exp2f(m2 - mm);
             l = l * f1 + mine[NR + 1][lane] * f2;
 #pragma unroll

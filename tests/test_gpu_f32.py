@@ -39,6 +39,56 @@ def tm():
     return binding
 
 
+def _overflow(x, blocked, sign):
+    """Rows of q (sign 0) or k whose scores overflow to -inf in fp32 where ``blocked``."""
+    if sign == 0:
+        return np.abs(x) * np.float32(1e20)
+    y = x * np.float32(1e-20)
+    y[:, blocked] = np.float32(-1e20)
+    return y
+
+
+# D, T, C, R, W, frames (sequence), chunk (streamed): 4 key groups at D = 128, 8 at 64
+@pytest.mark.parametrize("D,T,C,R,W,frames,chunk", [(128, 50, 2, 1, 2, 9, 3), (64, 50, 2, 1, 2, 9, 3)])
+@pytest.mark.parametrize("where", ["late", "alternate", "early"])
+def test_f32_scores_of_minus_infinity(tm, D, T, C, R, W, frames, chunk, where):
+    # Finite inputs whose scores overflow to -inf: over whole key groups ("late": from
+    # the 100th key on), over the first block of some groups only ("alternate": every
+    # other 32 keys), and over the row's first keys. They weigh nothing.
+    say(f"f32 -inf: D={D} {where}")
+    B, H = 1, 2
+    g = ChunkGeometry(T, C, R, W)
+    desc = tm.make_desc(B, H, D, T, C, R, W, "f32")
+    blocked = {"late": lambda p: p >= 100, "alternate": lambda p: p // 32 % 2 == 1, "early": lambda p: p < 40}[where]
+    w = Workload(750, "f32_inf", "f32", B, H, D, T, C, R, W, n_frames=frames)
+    d = draw_qkv_sequence(w)
+    d["q"] = _overflow(d["q"], None, 0)
+    d["k"] = _overflow(d["k"], blocked(np.arange(frames * T)), 1)
+    q, k, v = (to_dev(d[n]) for n in "qkv")
+    lse = torch.empty(B, H, frames * T, dtype=torch.float32, device="cuda")
+    o = tm.tm_sparse_causal_attn_fwd(desc, q, -1, k=k, v=v, n_frames=frames, lse=lse)
+    torch.cuda.synchronize()
+    with np.errstate(over="ignore"):
+        want, want_lse = full_sequence_attention(d["q"], d["k"], d["v"], g)
+    assert_close(from_dev(o), want, "f32", "sequence")
+    assert np.max(np.abs(lse.cpu().numpy() - want_lse)) <= LSE_ATOL["f32"]
+
+    cache, hist, seen = tm.KVCache(desc), StreamHistory(g), 0
+    for t in range(chunk + 1):
+        c = draw_chunk(w, t)
+        n = c["k"].shape[1]
+        c["q"] = _overflow(c["q"], None, 0)
+        c["k"] = _overflow(c["k"], blocked(seen + np.arange(n)), 1)
+        seen += n
+        qd, kd, vd = (to_dev(c[x]) for x in "qkv")
+        tm.tm_kv_append(cache, t, kd, vd)
+        hist.append(t, c["k"], c["v"])
+        o = from_dev(tm.tm_sparse_causal_attn_fwd(desc, qd, t, cache=cache))
+    with np.errstate(over="ignore"):
+        want = hist.attend(c["q"], chunk)[0]
+    assert_close(o, want, "f32", "stream")
+
+
 def _heads(B, H):
     """(batch, head) pairs to compare: all of a small case, the corners of a large one."""
     if B * H <= 16:
