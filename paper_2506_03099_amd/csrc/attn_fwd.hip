@@ -428,6 +428,10 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
 #pragma unroll
     for (int i = 0; i < DB; ++i) acc[i] = f32x16_t{};
     float m_run;            // running max in the scaled log2 domain (lazy)
+    // Lanes whose row has had no finite score yet. Their running max is 0, so that
+    // scores of -inf add nothing; the first tile that has a finite score sets it to
+    // its own maximum, which may be far below.
+    uint64_t fresh = 0;
     float l_run = 0.f;      // this lane's partial row sum
     const float c = a.scale_log2;
     // S^T output layout: register i of block kb holds key 32*kb + (VT ?
@@ -528,10 +532,9 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
 #pragma unroll
         for (int s = 0; s < NK; ++s) xa[s & 1] = mfma32x32x16(kf[s], qf[s >> 1], xa[s & 1]);
         mask_tile(xa, first);
-        // (a row whose scores are all -inf here starts from 0, so that it adds
-        // nothing to the rows' sums instead of making them NaN)
         const float mx = row_max(xa);
         m_run = mx == kNegInf ? 0.f : mx * c;
+        fresh = __ballot(mx == kNegInf);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -642,9 +645,12 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
             for (int e = EPG * g; e < EPG * (g + 1); e += 2) form_p2(x, pf, e, (e & 2) ? lt1 : lt0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (__builtin_expect(__any(!(lt0 + lt1 <= 0x1p16f)), 0)) {
-            const float dm = fmaxf(row_max(x), 0.f);
-            const float alpha = __builtin_amdgcn_exp2f(-dm);
+        if (__builtin_expect((__ballot(!(lt0 + lt1 <= 0x1p16f)) | fresh) != 0, 0)) {
+            const float mx = row_max(x);
+            const bool first = __builtin_amdgcn_inverse_ballot_w64(fresh) && mx != kNegInf;
+            const float dm = first ? mx : fmaxf(mx, 0.f);
+            const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-dm);  // (sum and O are still 0)
+            fresh &= __ballot(mx == kNegInf);
             m_run += dm;
             l_run *= alpha;
 #pragma unroll
@@ -663,6 +669,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
         if (turn) {  // tile t+1 starts a part: its exact maximum, as in the prologue
             const float mx = row_max(nx);
             nm = mx == kNegInf ? 0.f : -(mx * c);
+            fresh = __ballot(mx == kNegInf);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -154,6 +154,55 @@ def test_split_parts_of_minus_infinity(tm):
     _both(tm, desc, q, -1, [0], want, mag, want_lse, "-inf parts", k=k, v=v, n_frames=4)
 
 
+def _low_scores(d, blocked):
+    """q and k whose scores lie near -300 in the log2 domain, or at -inf where
+    ``blocked`` (keys): dimension 0 carries the offset, the others are as drawn."""
+    D = d["q"].shape[-1]
+    d["q"][..., 0] = 64.0
+    d["k"][..., 0] = np.float32(-300 * np.log(2) * np.sqrt(D) / 64)
+    d["k"][:, blocked, :, 0] = -3e38  # times 64: past the largest fp32
+    for n in "qk":
+        d[n + "_bits"] = f32_to_bf16_bits(d[n])
+        d[n] = bf16_bits_to_f32(d[n + "_bits"])
+    return d
+
+
+@pytest.mark.parametrize("D", [128, 64])
+def test_split_parts_that_start_at_minus_infinity(tm, D):
+    # Two of three 64-key tiles score -inf: most parts start with one and go on with
+    # scores far below 0, which weigh as much as those of the other parts.
+    say(f"split parts that start at -inf: D={D}")
+    blocked = lambda p: p // 64 % 3 != 2  # noqa: E731
+    B, H, T, C, R, W, frames = 1, 2, 256, 3, 1, 1, 8
+    g = ChunkGeometry(T, C, R, W)
+    desc = tm.make_desc(B, H, D, T, C, R, W, "bf16")
+    d = draw_qkv_sequence(Workload(890, "split", "bf16", B, H, D, T, C, R, W, n_frames=frames))
+    d = _low_scores(d, blocked(np.arange(frames * T)))
+    q, k, v = (to_dev(d[n], d[n + "_bits"], "bf16") for n in "qkv")
+    assert _bytes(tm, desc, -1, None, frames) > 0
+    with np.errstate(over="ignore"):
+        want, want_lse = full_sequence_attention(d["q"], d["k"], d["v"], g)
+        mag = full_sequence_attention(d["q"], d["k"], np.abs(d["v"]), g)[0]
+    _both(tm, desc, q, -1, [0, 1], want, mag, want_lse, "sequence", k=k, v=v, n_frames=frames)
+
+    w = Workload(891, "split", "bf16", B, H, D, T, C, R, W)
+    cache, hist, hist_abs, seen = tm.KVCache(desc), StreamHistory(g), StreamHistory(g), 0
+    for t in range(4):
+        d = draw_chunk(w, t)
+        n = d["k"].shape[1]
+        d = _low_scores(d, blocked(seen + np.arange(n)))
+        seen += n
+        q, k, v = (to_dev(d[x], d[x + "_bits"], "bf16") for x in "qkv")
+        tm.tm_kv_append(cache, t, k, v)
+        hist.append(t, d["k"], d["v"])
+        hist_abs.append(t, d["k"], np.abs(d["v"]))
+    assert _bytes(tm, desc, 3, cache) > 0
+    with np.errstate(over="ignore"):
+        want, want_lse = hist.attend(d["q"], 3)
+        mag = hist_abs.attend(d["q"], 3)[0]
+    _both(tm, desc, q, 3, [0, 1], want, mag, want_lse, "stream", cache=cache)
+
+
 def test_split_off_the_current_stream_and_under_capture(tm):
     # neither takes a workspace: the bits of the call without one, replay after replay
     desc = tm.make_desc(1, 2, 128, 256, 3, 1, 1, "bf16")
