@@ -41,6 +41,7 @@
 // operands loaded from global memory by the lanes that feed them; the keys of a
 // query tile may be shared out over a workgroup's waves.
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -997,10 +998,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
     f32x16_t acc[DB];
 #pragma unroll
     for (int d = 0; d < DB; ++d) acc[d] = f32x16_t{};
-    // Running max of the row (log2 domain), what the exponents subtract (0 while
-    // the row has only seen scores of -inf, which then add nothing), this lane's
-    // part of the row's sum.
-    float m = kNegInf, ms = 0.f, l = 0.f;
+    // Running max of the row (log2 domain), this lane's part of its sum. The max
+    // starts from the lowest finite value, from which scores of -inf add nothing
+    // (from -inf they would make the sum NaN).
+    float m = -FLT_MAX, l = 0.f;
     const float c = a.scale_log2;
     if (busy) {
         const float* row = k_base(k0, ke);
@@ -1044,8 +1045,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
             const float m_new = fmaxf(m, fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c);
             if (__any(m_new > m)) {
-                ms = m_new == kNegInf ? 0.f : m_new;
-                const float alpha = __builtin_amdgcn_exp2f(m - ms);
+                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
                 l *= alpha;
 #pragma unroll
                 for (int d = 0; d < DB; ++d) acc[d] *= alpha;
@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                s0[i] = __builtin_amdgcn_exp2f(fmaf(s0[i], c, -ms));
+                s0[i] = __builtin_amdgcn_exp2f(fmaf(s0[i], c, -m));
                 l += s0[i];
             }
 #pragma unroll
@@ -1087,8 +1087,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_fwd_f32_kernel(
         if (kg < half) {
             const float m2 = mine[NR][lane];
             const float mm = fmaxf(m, m2);
-            // a group without keys, or whose scores are all -inf, has l = 0 and O = 0
-            const float f1 = m == kNegInf ? 0.f : exp2f(m - mm), f2 = m2 == kNegInf ? 0.f : exp2f(m2 - mm);
+            // (a group without keys, or whose scores are all -inf, has l = 0 and O = 0)
+            const float f1 = exp2f(m - mm), f2 = exp2f(m2 - mm);
             l = l * f1 + mine[NR + 1][lane] * f2;
 #pragma unroll
             for (int i = 0; i < NR; ++i) acc[i / 16][i % 16] = acc[i / 16][i % 16] * f1 + mine[i][lane] * f2;
