@@ -275,14 +275,16 @@ def _fwd(desc, q, q_chunk, cache, k, v, n_frames, o, o_f32, lse, stream):
     h = cache.handle if cache is not None else None
     d = ctypes.byref(desc)
     L = lib()
+    # (the tensors first: on a host without a GPU there is no stream to ask for)
+    pq, pk, pv, po, pl = _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse)
     stream = _stream(stream)
     ws, n = None, 0
     if desc.dtype == TM_BF16:
         n = L.tm_sparse_causal_attn_fwd_workspace(d, q_chunk, h, n_frames)
         if n:
             ws = _workspace(n, q, stream)
-    _check(L.tm_sparse_causal_attn_fwd_ws(d, _ptr(q), q_chunk, h, _ptr(k), _ptr(v), n_frames, _ptr(o),
-                                          o_f32, _ptr(lse), _ptr(ws), n, stream))
+    _check(L.tm_sparse_causal_attn_fwd_ws(d, pq, q_chunk, h, pk, pv, n_frames, po, o_f32, pl, _ptr(ws), n,
+                                          stream))
     return o
 
 
@@ -353,12 +355,11 @@ def tm_sparse_causal_attn_bwd(desc: tm_attn_desc, n_frames: int, q, k, v, o, lse
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     d = ctypes.byref(desc)
+    ptrs = [_ptr(t) for t in (q, k, v, o, lse, dout, delta, dq, dk, dv)]
     stream = _stream(stream)
     n = lib().tm_sparse_causal_attn_bwd_workspace(d, n_frames)
     ws = _workspace(n, q, stream)
-    _check(lib().tm_sparse_causal_attn_bwd_ws(d, n_frames, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
-                                              _ptr(dout), _ptr(delta), _ptr(dq), _ptr(dk), _ptr(dv),
-                                              _ptr(ws), n, stream))
+    _check(lib().tm_sparse_causal_attn_bwd_ws(d, n_frames, *ptrs, _ptr(ws), n, stream))
     return dq, dk, dv
 
 

@@ -11,6 +11,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import ChunkGeometry, allowed_mask
 from oracle.attention import chunk_start
@@ -214,3 +215,24 @@ def test_backward_rejects_bad_arguments(tm):
     assert call(d, 21) == tm.TM_E_ARG                 # not device memory
     assert L.tm_sparse_causal_attn_bwd(None, 21, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE,
                                        FAKE, None) == tm.TM_E_ARG
+
+
+# --------------------------------------------------------------------------- the binding
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_binding_rejects_host_tensors(tm, dtype):
+    # with and without a GPU in the machine: no stream is asked for before the tensors are checked
+    d = tm.make_desc(1, 2, 64, 64, 2, 1, 1, dtype)
+    x = torch.zeros((1, 192, 2, 64), dtype=d.torch_dtype)
+    lse = torch.zeros((1, 2, 192))
+    calls = [
+        lambda: tm.tm_sparse_causal_attn_fwd(d, x, -1, k=x, v=x, n_frames=3),
+        lambda: tm.tm_sparse_causal_attn_fwd_f32out(d, x, -1, k=x, v=x, n_frames=3, lse=lse),
+        lambda: tm.tm_sparse_causal_attn_bwd(d, 3, x, x, x, x, lse, x),
+        lambda: tm.tm_sparse_causal_attn_bwd_noalloc(d, 3, x, x, x, x, lse, x, x, x, x),
+    ]
+    for call in calls:
+        with pytest.raises(tm.TMError) as e:
+            call()
+        assert e.value.status == tm.TM_E_ARG
