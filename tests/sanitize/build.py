@@ -1,6 +1,6 @@
-"""Build the sanitizer driver of the C ABI: tm_api.cpp (the host side of the
-library) and host_abi_driver.cpp compiled by g++ with AddressSanitizer and
-UndefinedBehaviorSanitizer into one executable, which takes the device
+"""Build the sanitizer driver of the C ABI: host_abi_driver.cpp, which includes
+tm_api.cpp (the host side of the library), compiled by g++ with AddressSanitizer
+and UndefinedBehaviorSanitizer into one executable, which takes the device
 kernels' launchers from the built libtm.so. Host code only: the kernels are
 not instrumented.
 
@@ -26,21 +26,17 @@ CXXFLAGS = ["-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__", "-I", os.path.j
 def build(verbose: bool = False) -> str:
     if not os.path.exists(os.path.join(PKG, "libtm.so")):
         raise RuntimeError("libtm.so must be built first")
-    objs = []
-    for src in (os.path.join(PKG, "csrc", "tm_api.cpp"), os.path.join(HERE, "host_abi_driver.cpp")):
-        obj = os.path.join(HERE, os.path.basename(src) + ".o")
-        cmd = ["g++", *CXXFLAGS, *SAN, "-c", src, "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        subprocess.run(cmd, check=True)
-        objs.append(obj)
-    cmd = ["g++", *SAN, *objs, "-L", PKG, "-ltm", "-L", os.path.join(ROCM, "lib"), "-lamdhip64",
+    obj = os.path.join(HERE, "host_abi_driver.o")
+    cmd = ["g++", *CXXFLAGS, *SAN, "-c", os.path.join(HERE, "host_abi_driver.cpp"), "-o", obj]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    cmd = ["g++", *SAN, obj, "-L", PKG, "-ltm", "-L", os.path.join(ROCM, "lib"), "-lamdhip64",
            "-Wl,-rpath," + PKG, "-Wl,-rpath," + os.path.join(ROCM, "lib"), "-o", DRIVER]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
-    for obj in objs:
-        os.remove(obj)
+    os.remove(obj)
     return DRIVER
 
 

@@ -1,22 +1,25 @@
 // Driver of the C ABI (include/tm.h) for the sanitizer build: tm_api.cpp is
 // compiled with AddressSanitizer and UndefinedBehaviorSanitizer (host code
-// only) into this executable, which links the kernels from libtm.so. Every
+// only) into this file, so that its planners can be called here as well, and
+// the executable takes the kernels from libtm.so. Every
 // host path of the ABI runs here: descriptor and argument validation, the cache
 // size arithmetic, the key-range planner's pair counts (closed forms of the
 // chunk pattern, TalkingMachines Sec. 4.2), the limits of every size, and with
 // --gpu the cache bookkeeping, appends, forward, backward and audio calls on
 // real device memory. Exit status 0 and "host ABI driver: all checks passed"
-// when every check holds; a sanitizer report aborts the run.
+// when every check holds; a sanitizer report aborts the run. With --plan it
+// prints how a forward or backward call is laid out (see print_plan).
 #include <hip/hip_runtime.h>
 
 #include <climits>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 
-#include "tm.h"
+#include "../../paper_2506_03099_amd/csrc/tm_api.cpp"
 
 namespace {
 
@@ -209,6 +212,131 @@ void host_checks() {
                                           static_cast<float*>(FAKE), nullptr) == TM_E_ARG);
 }
 
+// A cache whose latest chunk is `chunk`, all chunks full but it (`rows`). No pools.
+tm_kv_cache planned_cache(const tm_attn_desc& d, const Geo& g, int32_t chunk, int32_t rows) {
+    tm_kv_cache c{};
+    c.desc = d;
+    tm_kv_cache_reset(&c);
+    c.latest = chunk;
+    c.ref_len = chunk == 0 ? rows : int32_t(g.RT);
+    for (int64_t j = std::max<int64_t>(1, chunk - g.W); j <= chunk; ++j) {
+        const int slot = int((j - 1) % (g.W + 1));
+        c.slot_chunk[slot] = int32_t(j);
+        c.slot_len[slot] = j == chunk ? rows : int32_t(g.CT);
+    }
+    return c;
+}
+
+// The workspace queries and what the kernels are told, over the range of sizes:
+// the planners' sums and products must not overflow (UndefinedBehaviorSanitizer),
+// and the launches they describe must hold together.
+void plan_checks() {
+    EXPECT(tm_sparse_causal_attn_fwd_workspace(nullptr, -1, nullptr, 21) == 0);
+    EXPECT(tm_sparse_causal_attn_bwd_workspace(nullptr, 21) == 0);
+    tm_attn_desc bad = desc(1, 40, 96);
+    EXPECT(tm_sparse_causal_attn_fwd_workspace(&bad, -1, nullptr, 21) == 0);
+    EXPECT(tm_sparse_causal_attn_bwd_workspace(&bad, 21) == 0);
+    tm_attn_desc d = desc();
+    EXPECT(tm_sparse_causal_attn_fwd_workspace(&d, 8, nullptr, 21) == 0);   // no such chunk
+    EXPECT(tm_sparse_causal_attn_fwd_workspace(&d, -1, nullptr, 0) == 0);
+    EXPECT(tm_sparse_causal_attn_bwd_workspace(&d, 0) == 0);
+    EXPECT(tm_sparse_causal_attn_fwd_workspace(&d, -1, nullptr, INT32_MAX) == 0);
+    EXPECT(tm_sparse_causal_attn_bwd_workspace(&d, INT32_MAX) == 0);
+    tm_attn_desc f32 = desc(1, 1, 128, 256, 3, 1, 1, TM_F32);
+    EXPECT(tm_sparse_causal_attn_fwd_workspace(&f32, -1, nullptr, 21) == 0);  // its parts need none
+    EXPECT(tm_sparse_causal_attn_bwd_workspace(&f32, 21) == 0);
+
+    const int32_t bh[][2] = {{1, 1}, {1, 3}, {2, 5}, {1, 40}, {3, 67}, {1, 255}, {1, 257}, {1024, 1024}};
+    const int32_t geo[][5] = {  // T, C, R, W, frames (L below R * T, one token, the largest sizes, ...)
+        {1, 1, 1, 0, 1}, {7, 2, 5, 1, 3}, {64, 3, 1, 1, 21}, {256, 3, 1, 1, 21}, {1560, 3, 1, 1, 21},
+        {333, 7, 3, 12, 100}, {1 << 20, 1, 1, 12, 1 << 10}, {1 << 30, 1, 1, 0, 1}, {1, 1 << 26, 1 << 29, 12, 1 << 30}};
+    int split = 0, bsplit = 0;
+    for (const auto& b : bh)
+        for (int32_t D : {64, 128})
+            for (const auto& e : geo)
+                for (int32_t dt : {int32_t(TM_BF16), int32_t(TM_F32)}) {
+                    tm_attn_desc q = desc(b[0], b[1], D, e[0], e[1], e[2], e[3], dt);
+                    Geo g;
+                    if (check_desc(&q, &g) != TM_OK) continue;
+                    for (int form = 0; form < 3; ++form) {  // whole sequence, one chunk of it, streamed chunk
+                        const int32_t chunk = form == 0 ? -1 : form == 1 ? 0 : 2;
+                        tm_kv_cache cache{};
+                        if (form == 2) cache = planned_cache(q, g, 2, std::max<int32_t>(1, int32_t(g.CT - 1)));
+                        const tm_kv_cache* c = form == 2 ? &cache : nullptr;
+                        const int32_t frames = form == 2 ? 0 : e[4];
+                        Plan p;
+                        tmk::AttnArgs a{};
+                        if (make_plan(&q, chunk, c, frames, &g, &p) != TM_OK || plan_tiles(g, p, &a) != TM_OK) continue;
+                        const tmk::AttnSplit s = plan_split(g, p, a);
+                        const int64_t tiles = int64_t(a.n_qtiles) * g.B * g.H;
+                        EXPECT(s.whole >= 0 && s.whole <= tiles && s.parts >= 1 && s.parts <= tmk::kMaxParts);
+                        EXPECT((s.parts == 1) == (s.whole == tiles));
+                        EXPECT(s.parts == 1 || (s.whole % tmk::kCUs == 0 && (tiles - s.whole) * s.parts <= tmk::kCUs));
+                        EXPECT(tm_sparse_causal_attn_fwd_workspace(&q, chunk, c, frames) == split_bytes(g, a, s));
+                        EXPECT(dt == TM_BF16 || (s.parts == 1 && (a.key_groups == 1 || a.key_groups == 2 ||
+                                                                  a.key_groups == 4 || (a.key_groups == 8 && D == 64))));
+                        split += s.parts > 1;
+                    }
+                    const int64_t L = int64_t(e[4]) * g.T;
+                    tmk::BwdArgs k{};
+                    if (dt != TM_BF16 || L > kMaxTokens || plan_bwd_tiles(g, L, &k) != TM_OK) continue;
+                    const BwdParts n = plan_bwd_parts(g, L, &k);
+                    EXPECT(tm_sparse_causal_attn_bwd_workspace(&q, e[4]) == n.total());
+                    for (int32_t x : {k.k_ref_parts, k.k_chunk_parts, k.q_parts}) EXPECT(x >= 1 && x <= tmk::kMaxParts);
+                    EXPECT((n.dkdv > 0) == (k.k_ref_parts > 1 || (k.k_chunk_parts > 1 && k.k_tiles > k.k_ref_tiles)));
+                    EXPECT((n.dq > 0) == (k.q_parts > 1));
+                    // what the parts hold is bounded: two per CU of each kind of tile
+                    EXPECT(n.dkdv <= size_t(2 * 2 * tmk::kCUs) * 2 * 128 * D * 4 && n.dq <= size_t(2 * tmk::kCUs) * 128 * D * 4);
+                    bsplit += n.total() > 0;
+                }
+    EXPECT(split > 20 && bsplit > 10);
+
+    // argument checks of the calls with a workspace
+    float* F = static_cast<float*>(FAKE);
+    EXPECT(tm_sparse_causal_attn_fwd_ws(nullptr, FAKE, -1, nullptr, FAKE, FAKE, 21, FAKE, 0, nullptr, FAKE, 1 << 20,
+                                        nullptr) == TM_E_ARG);
+    EXPECT(tm_sparse_causal_attn_fwd_ws(&d, FAKE, 8, nullptr, FAKE, FAKE, 21, FAKE, 0, nullptr, nullptr, 0, nullptr) ==
+           TM_E_SHAPE);
+    EXPECT(tm_sparse_causal_attn_fwd_ws(&d, FAKE, -1, nullptr, FAKE, FAKE, 21, FAKE, 1, nullptr, nullptr, 0, nullptr) ==
+           TM_E_ARG);  // not device memory
+    EXPECT(tm_sparse_causal_attn_bwd_ws(&f32, 21, FAKE, FAKE, FAKE, FAKE, F, FAKE, F, FAKE, FAKE, FAKE, FAKE, 1 << 20,
+                                        nullptr) == TM_E_DTYPE);
+    EXPECT(tm_sparse_causal_attn_bwd_ws(&d, 21, FAKE, FAKE, FAKE, FAKE, F, FAKE, nullptr, FAKE, FAKE, FAKE, FAKE,
+                                        1 << 20, nullptr) == TM_E_ARG);  // delta
+    EXPECT(tm_sparse_causal_attn_bwd_ws(&d, 0, FAKE, FAKE, FAKE, FAKE, F, FAKE, F, FAKE, FAKE, FAKE, nullptr, 0,
+                                        nullptr) == TM_E_SHAPE);
+}
+
+// --plan DTYPE B H D T C R W seq FRAMES CHUNK | stream CHUNK ROWS | bwd FRAMES:
+// one line of "name value" pairs of the call's layout.
+int print_plan(int argc, char** argv) {
+    auto num = [&](int i) { return i < argc ? int32_t(std::atoi(argv[i])) : 0; };
+    tm_attn_desc d = desc(num(3), num(4), num(5), num(6), num(7), num(8), num(9),
+                          argc > 2 && std::strcmp(argv[2], "f32") == 0 ? TM_F32 : TM_BF16);
+    Geo g;
+    const char* form = argc > 10 ? argv[10] : "";
+    if (check_desc(&d, &g) != TM_OK) return 2;
+    if (std::strcmp(form, "bwd") == 0) {
+        tmk::BwdArgs a{};
+        if (plan_bwd_tiles(g, int64_t(num(11)) * g.T, &a) != TM_OK) return 2;
+        plan_bwd_parts(g, int64_t(num(11)) * g.T, &a);
+        std::printf("k_ref_parts %d k_chunk_parts %d q_parts %d\n", a.k_ref_parts, a.k_chunk_parts, a.q_parts);
+        return 0;
+    }
+    tm_kv_cache cache{};
+    const bool stream = std::strcmp(form, "stream") == 0;
+    if (stream) cache = planned_cache(d, g, num(11), num(12));
+    Plan p;
+    tmk::AttnArgs a{};
+    if (make_plan(&d, stream ? num(11) : num(12), stream ? &cache : nullptr, stream ? 0 : num(11), &g, &p) != TM_OK ||
+        plan_tiles(g, p, &a) != TM_OK)
+        return 2;
+    const tmk::AttnSplit s = plan_split(g, p, a);
+    std::printf("tiles %lld key_groups %d whole %lld parts %d\n", (long long)(int64_t(a.n_qtiles) * g.B * g.H),
+                a.key_groups, (long long)s.whole, s.parts);
+    return 0;
+}
+
 #define HIP_OK(x) EXPECT((x) == hipSuccess)
 
 // Device paths: the cache's bookkeeping through appends, overwrites, eviction
@@ -311,8 +439,10 @@ void gpu_checks() {
 }  // namespace
 
 int main(int argc, char** argv) {
+    if (argc > 1 && std::strcmp(argv[1], "--plan") == 0) return print_plan(argc, argv);
     const bool gpu = argc > 1 && std::strcmp(argv[1], "--gpu") == 0;
     host_checks();
+    plan_checks();
     if (gpu) gpu_checks();
     std::printf("host ABI driver (%s): %d checks, %d failed\n", gpu ? "host + gpu" : "host",
                 g_checks, g_failed);
