@@ -1,8 +1,9 @@
 """GPU parity of the split backward (the calls with a workspace).
 
 Tiles that do not fill the GPU share their sums out over several workgroups and
-another kernel adds the parts up. Each geometry runs with the workspace (the
-binding's ordinary call) and without (the C entry point that takes none), and
+another kernel adds the parts up (the sums of fp32 parts are ordered otherwise
+than those of the call without: not the same bits). Each geometry runs with the
+workspace (the binding's ordinary call) and without (the C entry point that takes none), and
 both are held to the oracle within the bound of the backward's other tests,
 |err| <= 2e-2 x RMS + 2^-8 |g| + 2^-8 m with m the sum of absolute products.
 """
@@ -37,12 +38,13 @@ def _bf16(rng, shape, norm):
 
 # B, H, D, T, C, R, W, frames, splits?
 CASES = [
-    (1, 1, 128, 100, 3, 1, 1, 11, True),   # dK/dV of c_0 and of the chunks, and dQ (c_0's tiles: empty parts)
+    (1, 1, 128, 100, 3, 1, 1, 11, True),   # dK/dV of c_0 and of the chunks
     (1, 2, 64, 70, 7, 2, 0, 16, True),     # D = 64, ragged tiles, two chunks
     (1, 3, 128, 131, 1, 1, 3, 9, True),    # the window reaches past the last chunk: short query ranges
     (2, 2, 128, 300, 2, 3, 1, 3, True),    # c_0 alone: every tile is one of its own
     (1, 24, 64, 130, 3, 1, 1, 13, True),   # only c_0's dK/dV
     (1, 2, 128, 50, 2, 1, 1, 5, False),    # too short
+    (1, 1, 128, 64, 7, 1, 1, 15, True),    # all three; c_0's query tile has one key tile: an empty part
 ]
 
 
@@ -81,6 +83,27 @@ def test_split_backward_matches_oracle(tm, B, H, D, T, C, R, W, frames, splits):
             assert worst <= 1.0, f"{route} {name}: error {worst:.3f} x the bound"
     for a, b in zip(got["workspace"], again):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+def test_split_backward_workspace_is_checked(tm):
+    desc = tm.make_desc(1, 1, 128, 100, 3, 1, 1, "bf16")
+    d, p = ctypes.byref(desc), tm._ptr
+    n = tm.lib().tm_sparse_causal_attn_bwd_workspace(d, 11)
+    assert n > 0
+    q, k, v, o, do, dq, dk, dv = (torch.zeros((1, 1100, 1, 128), dtype=torch.bfloat16, device="cuda") for _ in range(8))
+    lse, delta = (torch.zeros((1, 1, 1100), dtype=torch.float32, device="cuda") for _ in range(2))
+    call = lambda ws, size: tm.lib().tm_sparse_causal_attn_bwd_ws(  # noqa: E731
+        d, 11, p(q), p(k), p(v), p(o), p(lse), p(do), p(delta), p(dq), p(dk), p(dv), ws, size, tm._stream(None))
+    ws = torch.empty(n + 16, dtype=torch.uint8, device="cuda")
+    assert call(p(ws), n) == tm.TM_OK
+    assert call(p(ws), n - 1) == tm.TM_OK  # too small: not used
+    assert call(None, 0) == tm.TM_OK
+    assert call(p(ws) + 8, n) == tm.TM_E_ARG  # misaligned
+    assert call(p(ws) + (1 << 40), n) == tm.TM_E_ARG  # not device memory
+    big = torch.zeros(n + (1 << 20), dtype=torch.uint8, device="cuda")
+    q = big[:1100 * 256].view(torch.bfloat16)  # the workspace covers an input
+    assert call(p(big), n) == tm.TM_E_ARG
+    torch.cuda.synchronize()
 
 
 def test_split_backward_with_plain_addresses(tm):

@@ -1,10 +1,11 @@
 """GPU parity of the fp32 attention kernel where its key split changes.
 
 The kernel shares a query tile's keys out over 1, 2, 4 or 8 groups of waves,
-chosen on the host from the number of 32-row query blocks and of keys. Each
-case lands on one of them, streamed (dimension-major V from the cache) and as a
-whole sequence (row-major V), with ragged rows, ranges that end inside a
-32-key block and, in the stream, cache regions that start off 32-key blocks.
+chosen on the host from the number of 32-row query blocks and of keys. Each of
+CASES lands on one of them as a whole sequence (row-major V), each of STREAMS
+streamed (dimension-major V from the cache; test_plan.py holds the counts), with
+ragged rows, ranges that end inside a 32-key block and, in the stream, cache
+regions that start off 32-key blocks.
 Bar: max |gpu - oracle| <= 1e-4 x RMS, log-sum-exp within 1e-4.
 """
 import numpy as np
@@ -31,12 +32,42 @@ CASES = [
 ]
 
 
+# H, D, T, C, R, W, chunk: key groups of the streamed chunk (all rows). At D = 64, 8
+# groups where they share the 32-key blocks of the ranges about as evenly as 4 do.
+STREAMS = [
+    (2, 64, 50, 2, 1, 2, 3, 8),    # 14 blocks in 4 ranges
+    (2, 64, 64, 2, 1, 1, 2, 4),    # 10 blocks
+    (3, 64, 44, 2, 1, 2, 3, 4),    # 11 blocks, ragged ends
+    (1, 64, 64, 3, 1, 0, 1, 8),    # 8 blocks
+    (2, 128, 50, 2, 1, 2, 3, 4),   # D = 128: never 8
+]
+
+
 @pytest.fixture(scope="module")
 def tm():
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     from paper_2506_03099_amd import tm as binding
     binding.lib()
     return binding
+
+
+@pytest.mark.parametrize("H,D,T,C,R,W,chunk,groups", STREAMS)
+def test_f32_streamed_key_groups(tm, H, D, T, C, R, W, chunk, groups):
+    say(f"f32 stream: H={H} D={D} T={T} C={C} R={R} W={W} chunk={chunk} ({groups} key groups)")
+    g = ChunkGeometry(T, C, R, W)
+    desc = tm.make_desc(1, H, D, T, C, R, W, "f32")
+    w = Workload(760 + T, "f32_groups", "f32", 1, H, D, T, C, R, W)
+    cache, hist = tm.KVCache(desc), StreamHistory(g)
+    for t in range(chunk + 1):
+        c = draw_chunk(w, t)
+        qd, kd, vd = (to_dev(c[x]) for x in "qkv")
+        tm.tm_kv_append(cache, t, kd, vd)
+        hist.append(t, c["k"], c["v"])
+    lse = torch.empty(1, H, C * T, dtype=torch.float32, device="cuda")
+    o = from_dev(tm.tm_sparse_causal_attn_fwd(desc, qd, chunk, cache=cache, lse=lse))
+    want, want_lse = hist.attend(c["q"], chunk)
+    assert_close(o, want, "f32", "stream")
+    assert np.max(np.abs(lse.cpu().numpy() - want_lse)) <= LSE_ATOL["f32"]
 
 
 def _overflow(x, blocked, sign):

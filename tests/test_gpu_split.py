@@ -113,7 +113,7 @@ def test_split_stream(tm, B, H, D, T, C, R, W, rows, splits):
 
 # B, H, D, T, C, R, W, frames, splits?
 SEQUENCE = [
-    (1, 2, 128, 256, 3, 1, 1, 8, True),     # parts outnumber c_0's key tiles: some are empty
+    (1, 2, 128, 256, 3, 1, 1, 8, True),     # parts outnumber c_0's key tiles
     (1, 1, 64, 200, 2, 3, 2, 11, True),
     (2, 16, 128, 100, 2, 1, 1, 13, False),  # 256 tiles: a full round
 ]

@@ -1,10 +1,14 @@
 """The allocation-free backward (tm_sparse_causal_attn_bwd_noalloc), whose
 delta workspace is the library's device-global array, against the backward
-with a caller-owned workspace (tm_sparse_causal_attn_bwd): the same kernels,
-so the gradients must agree bit for bit. Two calls in a row, the second on a
-smaller problem, so that the second runs over what the first left in the
-array; sizes beyond the array are rejected before anything is launched.
+with a caller-owned delta (the C entry point tm_sparse_causal_attn_bwd): the
+same kernels, so the gradients must agree bit for bit. Three calls in a row, the
+later ones on smaller problems, so that they run over what the first left in
+the array; sizes beyond the array are rejected before anything is launched.
+(The binding's ordinary backward shares the sums of some sizes out over a
+workspace, the first call's among them: its sums are then ordered otherwise.)
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -32,7 +36,8 @@ def _bf16(rng, shape, norm):
 
 
 def test_noalloc_backward_equals_the_workspace_backward(tm):
-    for call, (B, H, D, T, C, R, W, frames) in enumerate([(2, 3, 128, 40, 2, 1, 1, 9),
+    for call, (B, H, D, T, C, R, W, frames) in enumerate([(1, 1, 128, 100, 3, 1, 1, 11),
+                                                          (2, 3, 128, 40, 2, 1, 1, 9),
                                                           (1, 2, 64, 24, 3, 1, 1, 5)]):
         say(f"noalloc backward call {call}: B={B} H={H} D={D} T={T} frames={frames}")
         rng = np.random.default_rng(70 + call)
@@ -42,13 +47,21 @@ def test_noalloc_backward_equals_the_workspace_backward(tm):
         desc = tm.make_desc(B, H, D, T, C, R, W, "bf16")
         lse = torch.empty(B, H, L, dtype=torch.float32, device="cuda")
         o = tm.tm_sparse_causal_attn_fwd(desc, q, -1, k=k, v=v, n_frames=frames, lse=lse)
-        want = tm.tm_sparse_causal_attn_bwd(desc, frames, q, k, v, o, lse, do)
+        d, p = ctypes.byref(desc), tm._ptr
+        assert (tm.lib().tm_sparse_causal_attn_bwd_workspace(d, frames) > 0) == (call == 0)
+        want, delta = tuple(torch.empty_like(q) for _ in range(3)), torch.empty_like(lse)
+        st = tm.lib().tm_sparse_causal_attn_bwd(d, frames, p(q), p(k), p(v), p(o), p(lse), p(do), p(delta),
+                                                *map(p, want), tm._stream(None))
+        assert st == tm.TM_OK, tm.tm_last_error()
+        if call > 0:  # not split: the binding's call as well
+            for g, w in zip(tm.tm_sparse_causal_attn_bwd(desc, frames, q, k, v, o, lse, do), want):
+                assert torch.equal(g.view(torch.int16), w.view(torch.int16))
         got = tuple(torch.full_like(q, float("nan")) for _ in range(3))
         tm.tm_sparse_causal_attn_bwd_noalloc(desc, frames, q, k, v, o, lse, do, *got)
         torch.cuda.synchronize()
         for name, g, w in zip(("dq", "dk", "dv"), got, want):
             same = torch.equal(g.view(torch.int16), w.view(torch.int16))
-            say(f"  {name}: bitwise equal to the workspace call: {same}")
+            say(f"  {name}: bitwise equal to the call with a delta: {same}")
             assert same, f"call {call}: {name} differs"
 
 
