@@ -459,8 +459,8 @@ __global__ __launch_bounds__(kDqThreads, 2) void bwd_dq_kernel(const BwdArgs a) 
 // dK, dV: per 128-key tile of one chunk, over the queries that see the chunk
 // ---------------------------------------------------------------------------
 // Each wave owns 32 keys and holds their K fragments (the B operand of
-// S = Q K^T) and their dK^T and dV^T accumulators in registers (about 240 per
-// lane, so two waves fit on a SIMD); the workgroup's V rows (the B operand of
+// S = Q K^T) and their dK^T and dV^T accumulators in registers (256 per lane at
+// D = 128, so two waves fit on a SIMD); the workgroup's V rows (the B operand of
 // dP = dO V^T) sit in LDS. The 32-query stages of Q, dO, lse and delta arrive
 // by direct global->LDS loads into two alternating buffers, the next stage's
 // loads in flight during the current stage's arithmetic; one barrier per
@@ -702,9 +702,10 @@ __global__ __launch_bounds__(kDkdvThreads, 2) void bwd_dkdv_kernel(const BwdArgs
             store_part<D>(p + 32 * D, dv, lane);
         } else {
             lds_u8* const rows = L + wave * 32 * ROWB;
-            store_rows<D>(rows, dk, a.scale, static_cast<__bf16*>(a.dk) + base + kw * st, st, k1 - kw, lane);
+            const int ln = fresh_thread_index() & 63;
+            store_rows<D>(rows, dk, a.scale, static_cast<__bf16*>(a.dk) + base + kw * st, st, k1 - kw, ln);
             asm volatile("" ::: "memory");
-            store_rows<D>(rows, dv, 1.f, static_cast<__bf16*>(a.dv) + base + kw * st, st, k1 - kw, lane);
+            store_rows<D>(rows, dv, 1.f, static_cast<__bf16*>(a.dv) + base + kw * st, st, k1 - kw, ln);
         }
     }
 }

@@ -82,13 +82,6 @@ __device__ __forceinline__ void wait_lds_dma_but() {
 // takes x as input and output, so the computation of x cannot be moved past
 // it (the compiler would otherwise sink work that is only used after a branch
 // or a barrier, away from the MFMAs it is meant to overlap).
-// threadIdx.x, which the compiler cannot fold into an earlier copy.
-__device__ __forceinline__ int fresh_thread_index() {
-    int v = static_cast<int>(threadIdx.x);
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 __device__ __forceinline__ float pin(float x) {
     asm volatile("" : "+v"(x));
     return x;
@@ -182,8 +175,8 @@ __device__ __forceinline__ f32x16_t mfma32x32x16(bf16x8_t a, bf16x8_t b, f32x16_
 // ----------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ----------------------------------------------------------------------------
-// LDS holds two K tiles and two V tiles (double buffering), each BN rows of D
-// bf16 with no padding. Every 16-byte chunk of a row sits at chunk position
+// LDS holds four K tiles and four V tiles, each BN rows of D bf16 with no
+// padding. Every 16-byte chunk of a row sits at chunk position
 // (chunk ^ swz(row)), which spreads both the K operand reads (same chunk of
 // consecutive rows) and the transposing V reads (two adjacent chunks of four
 // consecutive rows) over distinct banks. Tiles are filled by direct
@@ -766,6 +759,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
         constexpr int CM = OCPR < 16 ? 7 : 15;
         static_assert(NW * 32 * D * ES <= 2 * NBUF * TILEB, "output rows must fit the LDS");
         lds_u8* const rows = L + __builtin_amdgcn_readfirstlane(wave) * (32 * D * ES);
+        const int ln = fresh_thread_index() & 63, row_l = ln & 31, half = ln >> 5;
         if (busy) {
 #pragma unroll
             for (int d = 0; d < DB; ++d) {
@@ -775,12 +769,12 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
                         f32x4_t w;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) w[e] = acc[d][4 * g + e] * inv;
-                        *(lds_f32x4_t*)(rows + l32 * (D * ES) + (((8 * d + 2 * g + hw) ^ (l32 & CM)) << 4)) = w;
+                        *(lds_f32x4_t*)(rows + row_l * (D * ES) + (((8 * d + 2 * g + half) ^ (row_l & CM)) << 4)) = w;
                     } else {
                         bf16x4_t w;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(acc[d][4 * g + e] * inv);
-                        *(lds_bf16x4_t*)(rows + l32 * (D * ES) + (((4 * d + g) ^ (l32 & CM)) << 4) + 8 * hw) = w;
+                        *(lds_bf16x4_t*)(rows + row_l * (D * ES) + (((4 * d + g) ^ (row_l & CM)) << 4) + 8 * half) = w;
                     }
                 }
             }
@@ -788,7 +782,7 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
             unsigned char* const op = static_cast<unsigned char*>(a.o) + (bat * a.o_sb + head * a.o_sh) * ES;
 #pragma unroll
             for (int i = 0; i < 32 * OCPR / 64; ++i) {
-                const int ch = 64 * i + lane, row = ch / OCPR;
+                const int ch = 64 * i + ln, row = ch / OCPR;
                 const f32x4_t w = *(const lds_f32x4_t*)(rows + row * (D * ES) + (((ch % OCPR) ^ (row & CM)) << 4));
                 const int orow = tr.q0 + wave * 32 + row;
                 if (orow < tr.q1)

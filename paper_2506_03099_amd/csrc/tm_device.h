@@ -59,6 +59,14 @@ __device__ __forceinline__ int tr_swizzle(int row) {
     return D == 128 ? 4 * (row & 3) + ((row >> 2) & 3) : 4 * ((row >> 1) & 1) + ((row >> 2) & 3);
 }
 
+// threadIdx.x, which the compiler cannot fold into an earlier copy: what follows
+// from it is formed anew and not kept (spilled) since its first use.
+__device__ __forceinline__ int fresh_thread_index() {
+    int v = static_cast<int>(threadIdx.x);
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // s_waitcnt immediate (gfx9 encoding) for vmcnt(0), expcnt and lgkmcnt unconstrained.
 constexpr int kWaitVmcnt0 = 0x0F70;
 // s_waitcnt immediate for lgkmcnt(0), vmcnt and expcnt unconstrained.
