@@ -233,7 +233,7 @@ def main():
         "producer_frac_hbm": round(producer_bytes / (producer_ms * 1e-3) / 1e9 / PEAK_HBM_GBPS, 4),
         "timing": "warm: the chunk's K/V (224 MB) fit the 256 MB Infinity Cache",
         "roofline": {
-            "kernel": "attn_fwd_bf16_kernel<128, true>",
+            "kernel": "attn_fwd_bf16_kernel<128, true, false, 0>",
             "bound": "mfma",
             "achieved": round(attn_tflops, 2),
             "peak": PEAK_BF16_TFLOPS,
@@ -324,7 +324,7 @@ def audio_cross_attn(torch, tm, stream, steps):
     flop = sum(4.0 * w.head_dim * w.heads * int(per_frame[i].sum()) * keys[i]
                for i in range(w.n_frames)) * w.batch
     gbps = nbytes / (ms * 1e-3) / 1e9
-    return {"workload": w.name, "kernel": "audio_attn_bf16_kernel<128>", "bound": "hbm",
+    return {"workload": w.name, "kernel": "audio_attn_bf16_kernel<128, false, true, false>", "bound": "hbm",
             "us": round(ms * 1e3, 2), "algorithmic_mb": round(nbytes / 1e6, 2),
             "gbps": round(gbps, 1), "frac_hbm": round(gbps / PEAK_HBM_GBPS, 4),
             "face_fraction": round(face_rows / (w.batch * w.n_tok), 4),

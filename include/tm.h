@@ -229,9 +229,12 @@ tm_status tm_sparse_causal_attn_bwd(const tm_attn_desc* desc, int32_t n_frames, 
                                     hipStream_t stream);
 
 /* The same backward pass with a caller-owned workspace for the call's duration
- * on `stream`, as in tm_sparse_causal_attn_fwd_ws: tiles that do not fill the
- * GPU (c_0's keys, which every query sees, above all) then share their sums out
- * over several workgroups, whose fp32 parts are added up in a fixed order. */
+ * on `stream`, taken and checked as in tm_sparse_causal_attn_fwd_ws: tiles that
+ * do not fill the GPU (c_0's keys, which every query sees, above all) then share
+ * their sums out over several workgroups, whose fp32 parts a fourth launch adds
+ * up in a fixed order. That is another order of the fp32 sums than without a
+ * workspace: the results of the two calls differ by its rounding (here and there
+ * in the last bit of the bf16 gradients), each is deterministic. */
 size_t tm_sparse_causal_attn_bwd_workspace(const tm_attn_desc* desc, int32_t n_frames);
 tm_status tm_sparse_causal_attn_bwd_ws(const tm_attn_desc* desc, int32_t n_frames, const void* q,
                                        const void* k, const void* v, const void* o, const float* lse,
@@ -243,9 +246,10 @@ tm_status tm_sparse_causal_attn_bwd_ws(const tm_attn_desc* desc, int32_t n_frame
  * or harnesses that forbid allocation): delta lives in a device-global array
  * of the library, 8 MiB per GPU (room for B * H * L <= 2^21 rows), which each
  * GPU the library runs on holds until the process ends. Arguments, checks,
- * launches and results are those of tm_sparse_causal_attn_bwd without delta;
- * B * H * L above 2^21 returns TM_E_CAPACITY. The call allocates nothing.
- * Every call on one GPU uses that GPU's one array (each call writes delta
+ * launches and results, bit for bit, are those of tm_sparse_causal_attn_bwd
+ * without delta (not of tm_sparse_causal_attn_bwd_ws where that uses its
+ * workspace); B * H * L above 2^21 returns TM_E_CAPACITY. The call allocates
+ * nothing. Every call on one GPU uses that GPU's one array (each call writes delta
  * before reading it): calls that overlap in time on one GPU, on different
  * streams or from different threads, race and give wrong gradients; order
  * them. */

@@ -9,7 +9,8 @@
 //   dP = dO V^T,  dS = P * (dP - delta)
 //   dV = P^T dO,  dQ = scale dS K,  dK = scale dS^T Q
 //
-// Three kernels, all on the whole-sequence layout [B, L, H, D]:
+// Three kernels, all on the whole-sequence layout [B, L, H, D] (and
+// bwd_sum_kernel, which adds up the parts of split tiles):
 // - bwd_delta_kernel: delta [B, H, L] in fp32;
 // - bwd_dq_kernel: one workgroup of 4 waves per 128-row query tile (tiles
 //   never straddle a chunk, so a tile's rows share their key ranges); per

@@ -545,8 +545,9 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     // Stage 1: the score MFMAs of tile t+1, each with its share of P(t)
     // (exp2, bf16, row sum). Check: if some lane's row sum of the tile
     // exceeds 2^16 (a score more than 16 above the running max in the log2
-    // domain, or a non-finite value), raise the max to the tile's maximum,
-    // rescale O and the row sum, and form P(t) again. Stage 2: the P.V MFMAs
+    // domain, or a non-finite value), or has had no finite score yet, raise the
+    // max to the tile's maximum (from none: set it), rescale O and the row sum,
+    // and form P(t) again. Stage 2: the P.V MFMAs
     // of tile t, each with its share of x(t+1) = S(t+1)*c - m. Every MFMA is
     // preceded by the LDS read of the fragment RING MFMAs ahead; tile t+4 of
     // K and tile t+2 of V are loaded during stage 2. At the end each wave

@@ -482,7 +482,8 @@ tm_status plan_tiles(const Geo& g, const Plan& p, tmk::AttnArgs* out) {
 // half the CUs idle: 480p chunk (171 key tiles) with 1, 3, 5 heads: 205, 208,
 // 200 us whole, 45, 87, 128 split; 40-head reference frame (280 tiles over 25
 // key tiles): 90 -> 69. With more than half a round left over (8 heads, 152
-// tiles) one extra part for some tiles only lengthens the round. A part
+// tiles) one extra part for some tiles only lengthens the round (equal runs of key
+// tiles that go on over the ends of query tiles are not tried). A part
 // gets at least 4 key tiles (with 2 the merge costs more than the parts save:
 // reference frame +3 us), and the split has to shorten a tile by 10.
 tmk::AttnSplit plan_split(const Geo& g, const Plan& p, const tmk::AttnArgs& a) {
@@ -664,7 +665,9 @@ struct BwdParts {
 // chunk's tile, or of an evenly filled slot if that is longer (the 480p clip
 // with 40 heads: no split). The chunks' key tiles and the query tiles are split
 // only where all parts still fit the slots at a time (one head of that
-// sequence: 266 -> 80 us forward and backward). A part keeps 8 stages or 6 key
+// sequence: 266 -> 80 us forward and backward). Without a workspace nothing is
+// split: the parts in turn, as in the forward, gave the same bits but cost those
+// calls 4-13% with few heads (one head 194 -> 221 us). A part keeps 8 stages or 6 key
 // tiles, about what its start costs.
 BwdParts plan_bwd_parts(const Geo& g, int64_t L, tmk::BwdArgs* a) {
     constexpr int64_t kSlots = 2 * tmk::kCUs;  // workgroups of either kernel that run at a time

@@ -257,10 +257,11 @@ def tm_qkv_produce(cache: KVCache, chunk: int, q, k, v, q_gain=None, k_gain=None
 def _workspace(nbytes: int, q, stream: int):
     """A workspace for one call on `stream`: memory of torch's allocator, which
     hands it out again in the order of the current stream once the call has
-    returned. None (the call then runs without, to the same bits) where that
-    order does not cover the call: q a plain address or on another device than
-    the current one, another stream than the current one, or a stream under
-    capture; and where the memory is not to be had."""
+    returned. None (the call then runs without: the forward to the same bits, the
+    backward with its fp32 sums in another order) where that order does not cover
+    the call: q a plain address or on another device than the current one,
+    another stream than the current one, or a stream under capture; and where the
+    memory is not to be had."""
     if (nbytes == 0 or not isinstance(q, torch.Tensor)
             or q.get_device() != torch._C._cuda_getDevice()
             or stream != _current_stream() or torch.cuda.is_current_stream_capturing()):
@@ -348,7 +349,11 @@ def tm_audio_cross_attn_fwd_f32out(desc: tm_audio_desc, q, first_frame: int, ak,
 def tm_sparse_causal_attn_bwd(desc: tm_attn_desc, n_frames: int, q, k, v, o, lse, dout, delta=None,
                               dq=None, dk=None, dv=None, stream=None):
     """Gradients (dq, dk, dv) of the full-sequence sparse causal attention;
-    ``delta`` is an fp32 [B, H, L] workspace (allocated if not given)."""
+    ``delta`` is an fp32 [B, H, L] workspace (allocated if not given). Where the
+    sizes leave the GPU idle, the sums are shared out through a workspace of
+    torch's allocator; calls that can have none (under capture, on another stream
+    than the current one, with plain addresses) order them otherwise, as
+    ``tm_sparse_causal_attn_bwd_noalloc`` does."""
     if delta is None:
         delta = torch.empty_like(lse)
     dq = torch.empty_like(q) if dq is None else dq
