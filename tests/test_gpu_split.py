@@ -294,6 +294,39 @@ def test_split_bits_do_not_depend_on_the_workspace_sequence(tm, B, H, D, T, C, R
         _same_bits((inplace, lse[2]), want)
 
 
+def test_split_captured_chunk_has_the_eager_bits(tm):
+    # a streamed chunk's attention captured once, replayed on new queries each time, with
+    # eager calls in between; and the same call on a side stream
+    desc = tm.make_desc(1, 5, 128, 300, 3, 1, 1, "bf16")
+    w = Workload(895, "split", "bf16", 1, 5, 128, 300, 3, 1, 1)
+    cache = tm.KVCache(desc)
+    for t in range(4):
+        d = draw_chunk(w, t)
+        q, k, v = (to_dev(d[n], d[n + "_bits"], "bf16") for n in "qkv")
+        tm.tm_kv_append(cache, t, k, v)
+    assert _bytes(tm, desc, 3, cache) > 0
+    o, lse = torch.empty_like(q), torch.empty((1, 5, q.shape[1]), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tm.tm_sparse_causal_attn_fwd(desc, q, 3, cache=cache, o=o, lse=lse)
+    for i in range(4):
+        q.copy_(torch.roll(q, i + 1, 1))
+        want_lse = torch.empty_like(lse)
+        want = tm.tm_sparse_causal_attn_fwd(desc, q, 3, cache=cache, lse=want_lse)
+        o.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        _same_bits((o, lse), (want, want_lse))
+        side = torch.cuda.Stream()
+        o.zero_()
+        torch.cuda.synchronize()
+        tm.tm_sparse_causal_attn_fwd(desc, q, 3, cache=cache, o=o, lse=lse, stream=side)
+        torch.cuda.synchronize()
+        _same_bits((o, lse), (want, want_lse))
+
+
 def test_split_with_plain_addresses(tm):
     # tensors given as addresses: the call without a workspace
     desc = tm.make_desc(1, 2, 128, 256, 3, 1, 1, "bf16")
