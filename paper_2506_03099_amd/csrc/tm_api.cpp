@@ -19,9 +19,8 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
-#include <string>
+#include <new>
 #include <utility>
-#include <vector>
 
 #include "tm.h"
 #include "tm_internal.h"
@@ -38,15 +37,13 @@ struct tm_kv_cache {
 
 namespace {
 
-thread_local std::string g_err;
+thread_local char g_err[512];
 
 tm_status fail(tm_status st, const char* fmt, ...) {
-    char buf[512];
     va_list ap;
     va_start(ap, fmt);
-    vsnprintf(buf, sizeof(buf), fmt, ap);
+    vsnprintf(g_err, sizeof(g_err), fmt, ap);
     va_end(ap);
-    g_err = buf;
     return st;
 }
 
@@ -148,23 +145,41 @@ int64_t n_chunks(const Geo& g, int64_t L) {
 }
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Key ranges of one chunk's queries (held in place: planning allocates nothing,
+// so no exception can leave the C entry points).
+struct KeyRanges {
+    int n = 0;
+    std::pair<int64_t, int64_t> r[tmk::kMaxRanges];
+    static_assert(TM_MAX_WINDOW + 2 <= tmk::kMaxRanges, "c_0 and the window's chunks");
+    void add(int64_t b, int64_t e) { r[n++] = {b, e}; }
+    const std::pair<int64_t, int64_t>* begin() const { return r; }
+    const std::pair<int64_t, int64_t>* end() const { return r + n; }
+};
+
 struct Plan {
     int mode = 0;
     int64_t Lq = 0;
-    std::vector<std::pair<int64_t, int64_t>> ranges;  // mode 0
+    KeyRanges ranges;                                 // mode 0
     int64_t seq_len = 0;                              // mode 1
     int64_t pairs = 0;                                // allowed pairs per (b, h)
 };
 
 // Keys of query chunk a in a sequence of L tokens, as merged ranges.
-std::vector<std::pair<int64_t, int64_t>> sequence_ranges(const Geo& g, int64_t a, int64_t L) {
-    if (a == 0) return {{0, std::min(g.RT, L)}};
+KeyRanges sequence_ranges(const Geo& g, int64_t a, int64_t L) {
+    KeyRanges k;
     const int64_t lo = std::max<int64_t>(1, a - g.W);
-    if (lo == 1) return {{0, chunk_end(g, a, L)}};
-    return {{0, g.RT}, {chunk_start(g, lo), chunk_end(g, a, L)}};
+    if (a == 0) {
+        k.add(0, std::min(g.RT, L));
+    } else if (lo == 1) {
+        k.add(0, chunk_end(g, a, L));
+    } else {
+        k.add(0, g.RT);
+        k.add(chunk_start(g, lo), chunk_end(g, a, L));
+    }
+    return k;
 }
 
-int64_t range_len(const std::vector<std::pair<int64_t, int64_t>>& r) {
+int64_t range_len(const KeyRanges& r) {
     int64_t n = 0;
     for (const auto& x : r) n += x.second - x.first;
     return n;
@@ -195,21 +210,21 @@ tm_status plan_sequence(const Geo& g, int32_t n_frames, int32_t q_chunk, Plan* p
 
 tm_status plan_stream(const Geo& g, const tm_kv_cache* c, Plan* p) {
     const int32_t t = c->latest;
-    std::vector<std::pair<int64_t, int64_t>> r;
-    r.push_back({0, c->ref_len});
+    KeyRanges r;
+    r.add(0, c->ref_len);
     int64_t lq = c->ref_len;
     for (int64_t ch = std::max<int64_t>(1, t - g.W); ch <= t; ++ch) {
         const int slot = int((ch - 1) % (g.W + 1));
         if (c->slot_chunk[slot] != ch) return fail(TM_E_ORDER, "chunk %lld missing from the cache", (long long)ch);
         const int64_t b = g.ref_cap + slot * g.slot_cap;
-        r.push_back({b, b + c->slot_len[slot]});
+        r.add(b, b + c->slot_len[slot]);
         if (ch == t) lq = c->slot_len[slot];
     }
-    std::sort(r.begin(), r.end());
-    std::vector<std::pair<int64_t, int64_t>> m;
+    std::sort(r.r, r.r + r.n);
+    KeyRanges m;
     for (const auto& x : r) {
-        if (!m.empty() && m.back().second == x.first) m.back().second = x.second;
-        else m.push_back(x);
+        if (m.n > 0 && m.r[m.n - 1].second == x.first) m.r[m.n - 1].second = x.second;
+        else m.add(x.first, x.second);
     }
     p->mode = 0;
     p->Lq = lq;
@@ -414,13 +429,10 @@ tm_status plan_tiles(const Geo& g, const Plan& p, tmk::AttnArgs* out) {
     a.mode = p.mode;
     int64_t most_keys = 0;  // keys of the query row that sees the most
     if (p.mode == 0) {
-        if (p.ranges.size() > size_t(tmk::kMaxRanges))
-            return fail(TM_E_SHAPE, "too many key ranges (%zu)", p.ranges.size());
-        a.n_ranges = int32_t(p.ranges.size());
-        for (size_t i = 0; i < p.ranges.size(); ++i) {
-            a.range_begin[i] = int32_t(p.ranges[i].first);
-            a.range_end[i] = int32_t(p.ranges[i].second);
-            a.n_ktiles += int32_t(ceil_div(p.ranges[i].second - p.ranges[i].first, tmk::kKeyTile));
+        for (const auto& rg : p.ranges) {
+            a.range_begin[a.n_ranges] = int32_t(rg.first);
+            a.range_end[a.n_ranges++] = int32_t(rg.second);
+            a.n_ktiles += int32_t(ceil_div(rg.second - rg.first, tmk::kKeyTile));
         }
         most_keys = range_len(p.ranges);
     } else {
@@ -937,6 +949,6 @@ tm_status tm_audio_cross_attn_fwd_f32out(const tm_audio_desc* d, const void* q,
     return audio_fwd(d, q, first_frame, n_tok, ak, av, face, o, true, stream);
 }
 
-const char* tm_last_error(void) { return g_err.c_str(); }
+const char* tm_last_error(void) { return g_err; }
 
 }  // extern "C"

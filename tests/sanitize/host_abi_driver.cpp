@@ -21,6 +21,18 @@
 
 #include "../../paper_2506_03099_amd/csrc/tm_api.cpp"
 
+// With g_no_memory set, operator new fails on this thread.
+thread_local bool g_no_memory = false;
+void* operator new(size_t n) {
+    void* p = g_no_memory ? nullptr : std::malloc(n);
+    if (p == nullptr) throw std::bad_alloc();
+    return p;
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return g_no_memory ? nullptr : std::malloc(n); }
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+void operator delete(void* p, const std::nothrow_t&) noexcept { std::free(p); }
+
 namespace {
 
 int g_failed = 0;
@@ -290,6 +302,24 @@ void plan_checks() {
                     bsplit += n.total() > 0;
                 }
     EXPECT(split > 20 && bsplit > 10);
+
+    // no call that plans needs host memory: an exception must not cross the C ABI
+    {
+        tm_kv_cache full = planned_cache(d, Geo{1, 40, 128, 1560, 3, 1, 1, TM_BF16, 2, 1.f, 1560, 4680, 1560, 4680, 10944}, 5,
+                                         4000);
+        g_no_memory = true;
+        const size_t seq = tm_sparse_causal_attn_fwd_workspace(&d, -1, nullptr, 21);
+        const size_t stream = tm_sparse_causal_attn_fwd_workspace(&d, 5, &full, 0);
+        const size_t back = tm_sparse_causal_attn_bwd_workspace(&d, 21);
+        const int64_t pairs = tm_allowed_pairs(&d, -1, nullptr, 21), one = tm_allowed_pairs(&d, 5, &full, 0);
+        const tm_status shape = tm_sparse_causal_attn_fwd_ws(&d, FAKE, 8, nullptr, FAKE, FAKE, 21, FAKE, 0, nullptr, nullptr,
+                                                             0, nullptr);
+        const size_t message = std::strlen(tm_last_error());
+        g_no_memory = false;
+        EXPECT(seq == 0 && stream > 0 && back == 0);  // 40 heads: 640 tiles of the chunk, half a round over
+        EXPECT(pairs == 316368000 && one == int64_t(4000) * (1560 + 4680 + 4000));
+        EXPECT(shape == TM_E_SHAPE && message > 0);
+    }
 
     // argument checks of the calls with a workspace
     float* F = static_cast<float*>(FAKE);
