@@ -212,11 +212,11 @@ struct RowMerge {
 
 // A workgroup takes a query tile or a part of a split one. TURN > 0 (a call
 // without a workspace): TURN workgroups take a split tile, a share of its rows
-// and all of its parts in turn each. With one busy wave on a SIMD a key tile
-// takes 0.75 us there and not 1.1, and a part's end about 0.3, in a branch of the
-// one continuous walk (a walk of its own per part took 5 us for each: the tiles
-// in flight drain and the compiler spills): 480p chunk with 1, 3, 5 heads: 143,
-// 144, 148 us (44, 85, 130 with a workspace; 187, 190, 191 unsplit).
+// and all of its parts in turn each. Bound by a wave's own chain: with one busy
+// wave on a SIMD a key tile takes 0.8 us and not 1.1, and the parts' ends, in a
+// branch of the one continuous walk, hardly show. 480p chunk with 1, 3, 5 heads
+// (13, 4, 2 parts): 143, 144, 148 us; 44, 85, 130 with a workspace; 187, 190, 191
+// unsplit; 735, 361, 279 with a walk of its own per part.
 template <int D, bool VT, bool OF32, int TURN>
 __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const AttnArgs a) {
     constexpr int BM = kTileRowsBf16;  // query rows per workgroup
@@ -240,8 +240,9 @@ __global__ __launch_bounds__(kBf16Threads, 1) void attn_fwd_bf16_kernel(const At
     static_assert(NF % RING == 0 && NK >= RING && EPG % 2 == 0, "fragment ring layout");
 
     // K tile j sits in buffer j % 4 of the first four, V tile j in buffer
-    // j % 4 of the last four.
-    constexpr int SUMB = TURN > 0 ? NW / TURN * 32 * D * 4 : 0;  // O of the parts before, if there is room
+    // j % 4 of the last four; behind them, where there is room, O of the parts
+    // before (TURN).
+    constexpr int SUMB = TURN > 0 ? NW / TURN * 32 * D * 4 : 0;
     constexpr bool LSUM = SUMB > 0 && 2 * NBUF * TILEB + SUMB <= kMaxLds;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NBUF * TILEB + (LSUM ? SUMB : 0)];
     lds_u8* const L = (lds_u8*)(smem);
